@@ -14,6 +14,8 @@
 // so only forward substitutions are needed; they come out of the factorization itself when
 // the two vectors (S T_p)^T and (S T_q)^T are appended below the matrix as two extra rows.
 // Current: I = sum_k w_k T_k (midpoint quadrature, Sec. III C), sigma_I^2 = sum_k w_k^2 sigma_k^2.
+#include <algorithm>
+
 #include "common.h"
 
 namespace mcnegf {
@@ -308,37 +310,50 @@ __global__ void direct_prep_kernel(const double* __restrict__ P, const double* _
     v[3 * N + j] = sj;
 }
 
-// ---- Left-looking blocked Cholesky of the bordered probe system on FP64 matrix cores.
+// ---- Recursive blocked Cholesky of the bordered probe system on FP64 matrix cores.
 //
 // Per energy, logical rows 0..Np-1 are the scaled matrix padded with identity rows up to
 // Np = round_up(N, 16), rows Np and Np+1 are the two scaled right-hand sides; columns
-// 0..Np-1 are factored.  Block column J (columns c0 = 64 J .. c0 + wJ - 1):
-//   V  = A[c0:, J] - L[c0:, 0:c0] L[J, 0:c0]^T      (update, MFMA)
-//   L_JJ = chol(V_JJ),  Z = L_JJ^{-1}                (one wavefront, lane per row / column)
-//   L[below, J] = V_below L_JJ^{-T}   computed as (Z V_below^T)^T   (MFMA)
-// After the last block column, rows Np and Np+1 of L hold L^{-1} S T_p and L^{-1} S T_q.
-// One workgroup of 8 wavefronts per energy; each wavefront owns two 16-row tiles (w, w + 8) of a
-// 256-row super-tile and keeps their 16 x 64 updates in accumulators.  Block-column rows
-// L[J, 0:c0] are staged through LDS in 64-wide K chunks and serve as the MFMA A operand;
-// the tile rows stream from global memory as the B operand, so the accumulator holds the
-// transposed update, which is directly the B operand of the triangular-solve product.
+// 0..Np-1 are factored in panels of 128 columns.  Panel J (first column c0 = 128 J), all
+// energies of a launch together:
+//   factor  L_JJ = chol(V_JJ) and the inverses Z_b of its 16 x 16 diagonal sub-blocks,
+//           one workgroup per energy (the last panel's two bordered rows included);
+//   solve   L[below, J] = V[below, J] L_JJ^{-T};
+//   update  with m the largest power of two that divides J + 1, the next m panels get the
+//           contribution of the last m: V[i, j] -= sum_k L[i, k] L[j, k] over the 128 m
+//           columns k before column c1 = 128 (J + 1), for j in [c1, c1 + 128 m) and rows i >= j.
+//           m = 1 (odd panels) has no launch: the next factor and solve take that product.
+// The powers of two are the recursion V_22 - L_21 L_21^T by halves: each entry is read and
+// written once per set bit of its panel's index instead of once per panel, the products'
+// inner lengths are as long as their outer ones (a left-looking panel has few tiles of full
+// length at the end, a right-looking one a whole pass over the matrix per panel), and every
+// update has rows / 128 x m tiles per energy, enough to fill the chip with few energies.
+// Panel j >= 2 is first touched by the update with J + 1 = m, which reads the matrix itself
+// (panels 0 and 1 by their factor and solve).
+// The launch boundaries order the steps; no workgroup waits for another.
+// Measured against one workgroup per energy going left-looking through 64-column panels (split
+// over workgroups by panel rows with few energies), ms per factorization:
+//   N = 16000, 8 energies    418 -> 174  (63 TFLOP/s)     N = 4000, 64 energies   39.4 -> 27.3
+//   N = 3200, 128 energies  35.3 -> 29.3                  N = 1000, 256 energies  2.85 -> 2.83
+// (the split formed each diagonal block, a product over all previous columns, in every
+// workgroup, and the factor's serial chain of pivots took 24 us per 64 columns).
+//
 // v_mfma_f64_16x16x4f64 operand layouts (lane l, g = l / 16, n = l % 16):
 //   A[m][k]: m = n, k = g;   B[k][c]: k = g, c = n;   D[i][c] (item r): i = 4 r + g, c = n.
-// A lane's four accumulator items are therefore the columns 4 r + g of a 16-column block.
-// Rows of L are stored with the columns of every 16-column block permuted so that these
-// four items are contiguous (logical column 4 r + g at position 4 g + r, an involution):
-// the update contracts over stored positions of two rows of L, which any common column
-// permutation leaves unchanged, and the two bordered rows enter only through their dot
+// Column rows are the A operand and tile rows the B operand, so an accumulator holds the
+// transposed block: lane (n, g) has row n, columns 4 r + g, which is the B operand of the
+// next product.  Rows of L are stored with the columns of every 16-column block permuted so
+// that these four items are contiguous (logical column 4 r + g at position 4 g + r, an
+// involution): the update contracts over stored positions of two rows of L, which any common
+// column permutation leaves unchanged, and the two bordered rows enter only through their dot
 // product, which it leaves unchanged too.
 typedef double dmfma4 __attribute__((ext_vector_type(4)));
+typedef double dvec2 __attribute__((ext_vector_type(2)));
 
-constexpr int CH_NB = 64;            // block-column width
-constexpr int CH_KC = 32;            // K chunk staged in LDS (double-buffered)
-constexpr int CH_BP = CH_KC + 4;     // LDS pitch of a staged row (doubles)
-constexpr int CH_KG = CH_KC / 16;    // 16-column MFMA groups per chunk
-constexpr int CH_VP = CH_NB + 1;     // LDS pitch of the diagonal block
-constexpr int CH_WAVES = 8;
-constexpr int CH_ROWS = CH_WAVES * 32;  // rows per super-tile
+constexpr int CH_NB = 128;            // panel width
+constexpr int CH_SB = CH_NB / 16;     // 16-column sub-blocks of a panel
+constexpr int CH_NBLK = CH_SB * (CH_SB + 1) / 2;
+constexpr int CH_WAVES = 8;           // wavefronts of the factor and solve workgroups
 
 struct CholArgs {
     const double* P;      // [nE][N][ld] |G_ij|^2
@@ -351,395 +366,485 @@ struct CholArgs {
     int N, Np;
     int64_t ld;
     uint32_t inject_lead;
-    // Block columns [J0, J1) in this launch, and workgroups per energy.  One launch over all
-    // block columns (nsplit = 1) also forms T from the bordered rows as it goes; with several
-    // launches (one per block column, nsplit workgroups per energy taking every nsplit-th
-    // super-tile) T is formed afterwards by direct_dot_kernel.
-    int J0, J1, nsplit;
-    bool single;
+    int nE;
+    int J;      // panel
+    int m;      // update: panels per side
+    int tiles;  // solve: workgroups per energy; update: tiles per energy
+    int rows;   // solve: 16-row tiles per wavefront
 };
 
-__device__ inline double readlane_f64(double v, int lane) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-    return __hiloint2double(hi, lo);
-}
+// The factored matrix takes the sites of every 16-site block in the order of the involution
+// 4 r + g <-> 4 g + r (rows and columns alike), so that the four columns 4 r + g of a lane are
+// four consecutive sites, one 32-byte load of a row of P.
+__device__ inline int ch_site(int i) { return (i & ~15) + 4 * (i & 3) + ((i >> 2) & 3); }
 
-// Entries (i, c + 4 r), r = 0..3, of the bordered scaled matrix (lower part, c + 12 < Np).
-__device__ inline void aorig4(const CholArgs& a, const double* Pe, const double* ve, int i, int c,
-                              double (&out)[4]) {
+// Entries (i, cb + 4 r + g), r = 0..3, of the bordered scaled matrix (cb a multiple of 16).
+__device__ inline dmfma4 aorig4(const CholArgs& a, const double* Pe, const double* ve, int i,
+                                int cb, int g) {
     const int N = a.N;
-    if (i < N) {
-        const double* Pr = Pe + (size_t)i * a.ld;
-        const double ui = ve[i];
+    const int j = cb + 4 * g;  // the first of the four sites
+    dmfma4 out = dmfma4{0.0, 0.0, 0.0, 0.0};
+    if (i < a.Np) {
+        const int si = ch_site(i);
+        if (si < N) {
+            const double4 p = *reinterpret_cast<const double4*>(Pe + (size_t)si * a.ld + j);
+            const dmfma4 pv = dmfma4{p.x, p.y, p.z, p.w};
+            const double ui = ve[si];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = c + 4 * r;
-            const double uj = j < N ? ve[j] : 0.0;
-            const double pij = Pr[j];
-            out[r] = (j == i) ? 1.0 : (j < N ? -ui * uj * pij : 0.0);
+            for (int r = 0; r < 4; ++r) {
+                const double uj = ve[j + r];  // beyond N: the next vector's, not used
+                out[r] = j + r < N ? -ui * uj * pv[r] : 0.0;
+            }
         }
-    } else if (i < a.Np) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) out[r] = (c + 4 * r == i) ? 1.0 : 0.0;
+        for (int r = 0; r < 4; ++r) out[r] = j + r == si ? 1.0 : out[r];
     } else if (i < a.Np + 2) {
         const double* rhs = ve + (size_t)(i - a.Np + 1) * N;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) out[r] = (c + 4 * r < N) ? rhs[c + 4 * r] : 0.0;
-    } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) out[r] = 0.0;
+        for (int r = 0; r < 4; ++r) out[r] = j + r < N ? rhs[j + r] : 0.0;
     }
+    return out;
 }
 
-// Staging of a block-column row segment (4 doubles at column col) through registers into LDS.
-// Rows beyond R read row R - 1 and are then scaled by 0 (a select would let the compiler turn
-// the load into a predicated one, and the branch around it makes every later wait for any load
-// a wait for all of them, the prefetched tile rows included).  Such rows only feed results
-// that are never stored (rows or columns beyond the matrix), so a non-finite value there is
-// harmless.
-__device__ inline double4 stage_load(const double* Le, int64_t ld, int R, int row, int col) {
-    const bool ok = row < R;
-    const double4 v = *reinterpret_cast<const double4*>(Le + (size_t)(ok ? row : R - 1) * ld + col);
-    const double m = ok ? 1.0 : 0.0;
-    return double4{v.x * m, v.y * m, v.z * m, v.w * m};
+__device__ inline dmfma4 load4(const double* p) {
+    const double4 v = *reinterpret_cast<const double4*>(p);
+    return dmfma4{v.x, v.y, v.z, v.w};
+}
+__device__ inline void store4(double* p, dmfma4 v) {
+    *reinterpret_cast<double4*>(p) = double4{v[0], v[1], v[2], v[3]};
 }
 
-// MFMAs of one staged chunk for the first NT of a wavefront's two 16-row tiles: NCB 16-column
-// blocks of the block column (A operand from LDS), tile rows (B operand) from registers.
-template <int NCB, int NT = 2>
-__device__ inline void chunk_mfma(const double* B, const double4 (&av)[2][CH_KG],
-                                  dmfma4 (&acc)[2][4], int ln, int cq) {
+// c + A B for 16 x 16 blocks: one operand item per K-step.
+__device__ inline dmfma4 mfma16(dmfma4 a, dmfma4 b, dmfma4 c) {
 #pragma unroll
-    for (int kg = 0; kg < CH_KG; ++kg) {
-        double4 bf[NCB];
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-            bf[cb] = *reinterpret_cast<const double4*>(&B[(16 * cb + ln) * CH_BP + 16 * kg + cq]);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const double bv = q == 0 ? av[t][kg].x : q == 1 ? av[t][kg].y
-                                : q == 2 ? av[t][kg].z : av[t][kg].w;
-#pragma unroll
-                for (int cb = 0; cb < NCB; ++cb) {
-                    const double aval = q == 0 ? bf[cb].x : q == 1 ? bf[cb].y
-                                      : q == 2 ? bf[cb].z : bf[cb].w;
-                    acc[t][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(aval, bv, acc[t][cb], 0, 0, 0);
-                }
-            }
-        }
-    }
+    for (int r = 0; r < 4; ++r) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], b[r], c, 0, 0, 0);
+    return c;
 }
 
-__device__ inline void stage_store(double* Bs, int sm, int sc, const double4& b) {
-    *reinterpret_cast<double4*>(&Bs[sm * CH_BP + sc]) = b;
-}
-
-// The LDS arguments carry the LDS address space so that every access is a DS instruction: the
-// lanes exchange rows and columns through LDS, which a wavefront's DS instructions see in
-// program order (generic pointers would turn them into FLAT accesses, which give no such order).
+// The lower 16 x 16 sub-blocks (mb, kb) of a panel's diagonal block in LDS, without padding:
+// row n keeps its four 32-byte chunks (the columns 4 r + g of lane group g) rotated by n / 2,
+// which spreads the eight lanes of a 16-byte read over all banks.  The LDS address space is
+// carried in the type so that every access is a DS instruction.
 typedef __attribute__((address_space(3))) double lds_double;
-typedef __attribute__((address_space(3))) int lds_int;
-
-__device__ __noinline__ void factor_diag_block(lds_double* VZs, lds_double* Ls, lds_double* colbuf,
-                                               double* Lg, int64_t ld, int wJ, int lane,
-                                               lds_int* bad_flag, bool store) {
-    // Lane i holds row i; column k is shared through LDS.  The step branch is uniform; the
-    // updates of columns from wJ on are harmless (their entries stay zero).
-    const int i = lane;
-    double rw[CH_NB];
+__device__ inline int ch_blk(int mb, int kb) { return (mb * (mb + 1) / 2 + kb) * 256; }
+__device__ inline int ch_at(int n, int g) { return n * 16 + 4 * ((g + (n >> 1)) & 3); }
+__device__ inline dmfma4 lds_load4(const lds_double* p) { return dmfma4{p[0], p[1], p[2], p[3]}; }
+__device__ inline void lds_store4(lds_double* p, dmfma4 v) {
 #pragma unroll
-    for (int j = 0; j < CH_NB; ++j) rw[j] = (i < wJ && j < wJ && j <= i) ? VZs[i * CH_VP + j] : 0.0;
-    bool bad = false;
-#pragma unroll
-    for (int k = 0; k < CH_NB; ++k) {
-        if (k < wJ) {
-            double piv = readlane_f64(rw[k], k);
-            const bool good = piv > 0.0 && isfinite(piv);
-            bad |= !good;
-            piv = good ? piv : 1.0;
-            // one reciprocal square root and a product per lane: a shorter dependent chain
-            // per pivot than a square root followed by a division
-            const double rs = rsqrt(piv);
-            const double lik = (i >= k) ? rw[k] * rs : 0.0;
-            rw[k] = lik;
-            colbuf[i] = lik;
-#pragma unroll
-            for (int j = k + 1; j < CH_NB; ++j) {
-                rw[j] = fma(-lik, colbuf[j], rw[j]);
-            }
-        }
-    }
-    if (bad && lane == 0) *bad_flag = 1;
-#pragma unroll
-    for (int j = 0; j < CH_NB; ++j) {
-        const double lv = (j <= i && i < wJ) ? rw[j] : (i == j ? 1.0 : 0.0);
-        Ls[i * CH_VP + j] = lv;
-        if (store && j <= i && i < wJ)
-            Lg[(size_t)i * ld + (j & ~15) + 4 * (j & 3) + ((j >> 2) & 3)] = lv;
-    }
-    // Inverses of the four 16 x 16 diagonal sub-blocks of L_JJ: lane (b, c) = (lane / 16,
-    // lane % 16) computes column c of L_bb^{-1} by forward substitution and stores it in the
-    // diagonal sub-block b of V (Ls was written by this wavefront, whose LDS accesses stay in
-    // order).
-    const int b = lane >> 4, c = lane & 15;
-    const lds_double* Lb = Ls + (16 * b) * CH_VP + 16 * b;
-    double z[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        double s0 = (r == c) ? 1.0 : 0.0, s1 = 0.0;
-#pragma unroll
-        for (int m = 0; m + 1 < r; m += 2) {
-            s0 = fma(-Lb[r * CH_VP + m], z[m], s0);
-            s1 = fma(-Lb[r * CH_VP + m + 1], z[m + 1], s1);
-        }
-        if (r & 1) s0 = fma(-Lb[r * CH_VP + r - 1], z[r - 1], s0);
-        z[r] = (s0 + s1) / Lb[r * CH_VP + r];
-    }
-    lds_double* Zb = VZs + (16 * b) * CH_VP + 16 * b;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) Zb[r * CH_VP + c] = z[r];
+    for (int r = 0; r < 4; ++r) p[r] = v[r];
 }
 
-__global__ void __launch_bounds__(512) cholesky_kernel(CholArgs a) {
-    __shared__ double Bs[2][CH_NB * CH_BP];  // double-buffered K chunk of block-column rows
-    __shared__ double VZs[CH_NB * CH_VP];  // diagonal block V, then Z = L_JJ^{-1}
-    __shared__ double Ls[CH_NB * CH_VP];   // L_JJ
-    __shared__ double colbuf[CH_NB];
-    __shared__ double dot_acc;
-    __shared__ int bad_flag;
+// Forward substitution of one 16-row tile with the panel in LDS (Z_b in the diagonal
+// sub-blocks): y[b], block b of the tile's transposed rows, becomes block b of L.
+__device__ inline void panel_solve(const lds_double* S, dmfma4 (&y)[CH_SB], int nsb, int n, int g) {
+    const int at = ch_at(n, g);
+#pragma unroll
+    for (int kb = 0; kb < CH_SB; ++kb) {
+        if (kb < nsb) {
+            const dmfma4 x =
+                mfma16(lds_load4(S + ch_blk(kb, kb) + at), y[kb], dmfma4{0.0, 0.0, 0.0, 0.0});
+            y[kb] = x;
+            const dmfma4 xn = -x;
+#pragma unroll
+            for (int mb = kb + 1; mb < CH_SB; ++mb)
+                if (mb < nsb) y[mb] = mfma16(lds_load4(S + ch_blk(mb, kb) + at), xn, y[mb]);
+        }
+    }
+}
 
-    const int e = blockIdx.x / a.nsplit;
-    const int part = blockIdx.x - e * a.nsplit;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ln = lane & 15;
-    const int g = lane >> 4;
-    const int cq = 4 * g;
-    const int Np = a.Np;
-    const int R = Np + 2;
+// Position of Z_b among the unused upper sub-blocks of a full diagonal block.
+__device__ inline void z_home(int b, int& rb, int& cb) {
+    rb = b < CH_SB - 1 ? 0 : 1;
+    cb = b < CH_SB - 1 ? b + 1 : 2;
+}
+
+// Lane N of every row of 16 lanes, in all of them (one DPP move, no scalar registers).
+template <int N>
+__device__ inline double bcast16(double v) {
+    return __builtin_amdgcn_update_dpp(v, v, 0x150 + N, 0xF, 0xF, true);  // row_newbcast
+}
+
+// Pivots K .. 15 of a 16 x 16 sub-block: lane n of each row of 16 holds row n of the
+// sub-block (rw) and column n of the inverse of its factor (z).
+template <int K, int J>
+__device__ inline void factor_columns(double (&rw)[16], double (&z)[16], double lik) {
+    if constexpr (J < 16) {
+        const double ljk = bcast16<J>(lik);
+        rw[J] = fma(-lik, ljk, rw[J]);
+        z[J] = fma(-ljk, z[K], z[J]);
+        // the updates stay with their pivot: put off, the broadcasts would pile up and spill
+        asm volatile("" : "+v"(rw[J]), "+v"(z[J]));
+        factor_columns<K, J + 1>(rw, z, lik);
+    }
+}
+template <int K>
+__device__ inline void factor_pivots(double (&rw)[16], double (&z)[16], int n, bool& bad) {
+    if constexpr (K < 16) {
+        double piv = bcast16<K>(rw[K]);
+        const bool good = piv > 0.0 && isfinite(piv);
+        bad |= !good;
+        piv = good ? piv : 1.0;
+        // one reciprocal square root and products: a shorter dependent chain per pivot than a
+        // square root followed by divisions
+        const double rs = rsqrt(piv);
+        const double lik = n >= K ? rw[K] * rs : 0.0;
+        rw[K] = lik;
+        z[K] *= rs;
+        factor_columns<K, K + 1>(rw, z, lik);
+        factor_pivots<K + 1>(rw, z, n, bad);
+    }
+}
+
+// Cholesky factor of the diagonal block of panel J, one workgroup per energy.  Bound by the
+// serial chain of 128 pivots: wavefront 0 factors the 16 x 16 sub-blocks (lane per row, the
+// pivot column's entries by DPP broadcasts, which also feed the inverse's columns) while the
+// other wavefronts apply the previous sub-block's products to the rest.
+__global__ void __launch_bounds__(64 * CH_WAVES) cholesky_factor_kernel(CholArgs a) {
+    __shared__ double S_raw[CH_NBLK * 256];
+    lds_double* S = (lds_double*)S_raw;
+    const int e = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const int at = ch_at(n, g);
+    const int R = a.Np + 2;
     const int64_t ld = a.ld;
+    const int c0 = a.J * CH_NB;
+    const int nsb = min(CH_SB, (a.Np - c0) >> 4);
+    const bool last = c0 + CH_NB >= a.Np;
     const double* Pe = a.P + (size_t)e * a.N * ld;
     const double* ve = a.vec + (size_t)e * 4 * a.N;
     double* Le = a.Lall + (size_t)e * R * ld;
-    if (tid == 0) {
-        dot_acc = 0.0;
-        bad_flag = 0;
-    }
-    // staging assignment: row sm of the block column, 4 doubles at column sc of a chunk
-    const int sm = tid >> 3;
-    const int sc = (tid & 7) * 4;
-
-    for (int J = a.J0; J < a.J1; ++J) {
-        const int c0 = J * CH_NB;
-        const int wJ = min(CH_NB, Np - c0);
-        const int ncb = wJ >> 4;
-        // rows of L written below the previous diagonal block (by any wavefront) are read next
-        __syncthreads();
-
-        // ---- diagonal block: V_JJ = A_JJ - L[J, 0:c0] L[J, 0:c0]^T, both operands from LDS.
-        // Wavefront w owns the 16 x 16 blocks p = w and p = w + 8 (block row p / 4, column p % 4).
-        {
-            dmfma4 accd[2] = {dmfma4{0.0, 0.0, 0.0, 0.0}, dmfma4{0.0, 0.0, 0.0, 0.0}};
-            // chunk it + 1 is in registers while chunk it + 2 is loaded (two chunks ahead: this
-            // pass has little MFMA work to cover a load); loads past the last chunk re-read it
-            // and their data is never used, so neither loads nor stores are predicated
-            double4 bnext = {0.0, 0.0, 0.0, 0.0};
-            if (c0 > 0) {
-                stage_store(Bs[0], sm, sc, stage_load(Le, ld, R, c0 + sm, sc));
-                bnext = stage_load(Le, ld, R, c0 + sm, min(CH_KC, c0 - CH_KC) + sc);
-                __syncthreads();
+    double* Ld = Le + (size_t)c0 * ld + c0;
+    for (int q = wave; q < CH_NBLK; q += CH_WAVES) {
+        int mb = 0;
+        while ((mb + 1) * (mb + 2) / 2 <= q) ++mb;
+        const int kb = q - mb * (mb + 1) / 2;
+        if (mb < nsb) {
+            dmfma4 v = a.J <= 1 ? aorig4(a, Pe, ve, c0 + 16 * mb + n, c0 + 16 * kb, g)
+                                : load4(Ld + (size_t)(16 * mb + n) * ld + 16 * kb + 4 * g);
+            if (a.J & 1) {
+                const double* xr = Ld + (size_t)(16 * mb + n) * ld + 4 * g - CH_NB;
+                const double* xc = Ld + (size_t)(16 * kb + n) * ld + 4 * g - CH_NB;
+                dmfma4 acc = dmfma4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int k = 0; k < CH_SB; ++k) acc = mfma16(load4(xc + 16 * k), load4(xr + 16 * k), acc);
+                v -= acc;
             }
-            for (int kc = 0, it = 0; kc < c0; kc += CH_KC, ++it) {
-                const double* B = Bs[it & 1];
-                const double4 bst = bnext;
-                bnext = stage_load(Le, ld, R, c0 + sm, min(kc + 2 * CH_KC, c0 - CH_KC) + sc);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int p = wave + 8 * h;
-                    const int tb = p >> 2, cb = p & 3;
-                    if (cb <= tb && tb < ncb) {
-#pragma unroll
-                        for (int kg = 0; kg < CH_KG; ++kg) {
-                            const double4 av = *reinterpret_cast<const double4*>(
-                                &B[(16 * cb + ln) * CH_BP + 16 * kg + cq]);
-                            const double4 bv = *reinterpret_cast<const double4*>(
-                                &B[(16 * tb + ln) * CH_BP + 16 * kg + cq]);
-                            accd[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, bv.x, accd[h], 0, 0, 0);
-                            accd[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.y, bv.y, accd[h], 0, 0, 0);
-                            accd[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.z, bv.z, accd[h], 0, 0, 0);
-                            accd[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.w, bv.w, accd[h], 0, 0, 0);
-                        }
-                    }
-                }
-                stage_store(Bs[(it & 1) ^ 1], sm, sc, bst);  // unread after the last chunk
-                __syncthreads();
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int p = wave + 8 * h;
-                const int tb = p >> 2, cb = p & 3;
-                if (cb <= tb && tb < ncb) {
-                    double ao[4];
-                    aorig4(a, Pe, ve, c0 + 16 * tb + ln, c0 + 16 * cb + g, ao);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        VZs[(16 * tb + ln) * CH_VP + 16 * cb + 4 * r + g] = ao[r] - accd[h][r];
-                }
-            }
-        }
-        __syncthreads();
-        if (wave == 0)
-            factor_diag_block((lds_double*)VZs, (lds_double*)Ls, (lds_double*)colbuf,
-                              Le + (size_t)c0 * ld + c0, ld, wJ, lane, (lds_int*)&bad_flag,
-                              part == 0);
-        __syncthreads();
-
-        // ---- rows below the diagonal block, in super-tiles of 256 rows
-        for (int st = c0 + wJ + part * CH_ROWS; st < R; st += a.nsplit * CH_ROWS) {
-            // this wave's tiles: rows rw[t] .. rw[t] + 15 for t = 0, 1, tile wave + 8 t of the
-            // super-tile, so that a partial super-tile gives each wavefront at most one tile
-            // when it holds at most 8 (the wavefronts' MFMA work is then halved)
-            const int rw[2] = {st + 16 * wave, st + 16 * (wave + 8)};
-            dmfma4 acc[2][4];
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb) acc[t][cb] = dmfma4{0.0, 0.0, 0.0, 0.0};
-
-            // update: acc^T = L[tile rows, 0:c0] . L[J rows, 0:c0]^T.  Chunk it of the
-            // block-column rows is in Bs[it & 1] while chunk it + 1 is staged into the other
-            // buffer and this wavefront's tile rows of chunk it + 1 are loaded: one barrier per
-            // chunk, loads in flight across the chunk's MFMAs.
-            if (c0 > 0) {
-                double4 av[2][CH_KG];
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int kg = 0; kg < CH_KG; ++kg)
-                        av[t][kg] = stage_load(Le, ld, R, rw[t] + ln, 16 * kg + cq);
-                stage_store(Bs[0], sm, sc, stage_load(Le, ld, R, c0 + sm, sc));
-                __syncthreads();
-                // c0 = 64 J is a whole number of chunk pairs: the loop takes two chunks per
-                // iteration in straight-line code, the tile rows alternating between two
-                // register sets (chunk 2i multiplies av while an is loaded, chunk 2i + 1 the
-                // reverse) and the staged block-column rows between the two LDS buffers, so
-                // neither the loads nor the accumulators are copied.  All four 16-column
-                // blocks are multiplied (a narrower last block column's extra blocks are
-                // never stored), so the accumulators keep their registers.
-                double4 an[2][CH_KG];
-                for (int kc = 0; kc < c0; kc += 2 * CH_KC) {
-                    {
-                        const int kn = kc + CH_KC;  // always inside: c0 is a multiple of 64
-                        const double4 bst = stage_load(Le, ld, R, c0 + sm, kn + sc);
-#pragma unroll
-                        for (int t = 0; t < 2; ++t)
-#pragma unroll
-                            for (int kg = 0; kg < CH_KG; ++kg)
-                                an[t][kg] = stage_load(Le, ld, R, rw[t] + ln, kn + 16 * kg + cq);
-                        if (rw[1] < R) chunk_mfma<4, 2>(Bs[0], av, acc, ln, cq);
-                        else if (rw[0] < R) chunk_mfma<4, 1>(Bs[0], av, acc, ln, cq);
-                        stage_store(Bs[1], sm, sc, bst);
-                        __syncthreads();
-                    }
-                    {
-                        const bool more = kc + 2 * CH_KC < c0;
-                        const int kn = more ? kc + 2 * CH_KC : kc + CH_KC;
-                        const double4 bst = stage_load(Le, ld, R, c0 + sm, kn + sc);
-#pragma unroll
-                        for (int t = 0; t < 2; ++t)
-#pragma unroll
-                            for (int kg = 0; kg < CH_KG; ++kg)
-                                av[t][kg] = stage_load(Le, ld, R, rw[t] + ln, kn + 16 * kg + cq);
-                        if (rw[1] < R) chunk_mfma<4, 2>(Bs[1], an, acc, ln, cq);
-                        else if (rw[0] < R) chunk_mfma<4, 1>(Bs[1], an, acc, ln, cq);
-                        if (more) stage_store(Bs[0], sm, sc, bst);
-                        __syncthreads();
-                    }
-                }
-            }
-            // V = A - update (lane: row rw[t] + ln, columns c0 + 16 cb + 4 r + g), then
-            // X L_JJ^T = V by 16-column blocks: X_b^T = L_bb^{-1} (V_b^T - sum_{a<b} L_ba X_a^T),
-            // stored as rows of L.  V^T and X^T blocks are in accumulator layout, which is the
-            // B-operand layout of the next product.
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int rt = rw[t];
-                if (rt < R) {
-                    dmfma4 y[4];
-#pragma unroll
-                    for (int cb = 0; cb < 4; ++cb) {
-                        double ao[4];
-                        if (cb < ncb) aorig4(a, Pe, ve, rt + ln, c0 + 16 * cb + g, ao);
-                        else ao[0] = ao[1] = ao[2] = ao[3] = 0.0;
-                        // blocks beyond the block column's width hold the unused products of
-                        // the update: zero, as the bordered rows' dot product below reads them
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) y[cb][r] = cb < ncb ? ao[r] - acc[t][cb][r] : 0.0;
-                    }
-#pragma unroll
-                    for (int mb = 0; mb < 4; ++mb) {
-                        if (mb < ncb) {
-                            dmfma4 u = y[mb];
-#pragma unroll
-                            for (int kb = 0; kb < mb; ++kb)
-#pragma unroll
-                                for (int r = 0; r < 4; ++r) {
-                                    const double lv = Ls[(16 * mb + ln) * CH_VP + 16 * kb + 4 * r + g];
-                                    u = __builtin_amdgcn_mfma_f64_16x16x4f64(-lv, y[kb][r], u, 0, 0, 0);
-                                }
-                            dmfma4 x = dmfma4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const double zv = VZs[(16 * mb + ln) * CH_VP + 16 * mb + 4 * r + g];
-                                x = __builtin_amdgcn_mfma_f64_16x16x4f64(zv, u[r], x, 0, 0, 0);
-                            }
-                            y[mb] = x;
-                        }
-                    }
-                    const int row = rt + ln;
-                    if (row < R) {
-#pragma unroll
-                        for (int mb = 0; mb < 4; ++mb)
-                            if (mb < ncb)
-                                *reinterpret_cast<double4*>(Le + (size_t)row * ld + c0 + 16 * mb +
-                                                            cq) =
-                                    double4{y[mb][0], y[mb][1], y[mb][2], y[mb][3]};
-                    }
-                    if (a.single && rt == Np) {
-                        // rows Np (lanes ln == 0) and Np + 1 (ln == 1): accumulate y . z
-                        double part = 0.0;
-#pragma unroll
-                        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const double other = __shfl_down(y[mb][r], 1, 64);
-                                part = fma(y[mb][r], other, part);
-                            }
-                        part = ln == 0 ? part : 0.0;
-                        part += __shfl_xor(part, 16, 64);
-                        part += __shfl_xor(part, 32, 64);
-                        if (lane == 0) dot_acc += part;
-                    }
-                }
-            }
+            lds_store4(S + q * 256 + at, v);
         }
     }
     __syncthreads();
-    if (tid == 0) {
-        if (bad_flag) atomicOr(a.status, MCNEGF_FLAG_NOTSPD);
-        if (a.single) {
-            const double* ld_ = a.lead + (size_t)e * MCNEGF_LEAD_NTERMS;
-            const double tqp = a.inject_lead == 0 ? ld_[MCNEGF_LEAD_TRL] : ld_[MCNEGF_LEAD_TLR];
-            const double Tk = tqp + dot_acc;
-            a.T[e] = Tk;
-            a.sig[e] = 0.0;
-            if (!isfinite(Tk)) atomicOr(a.status, MCNEGF_FLAG_NONFINITE);
+    bool bad = false;
+    for (int b = 0; b < nsb; ++b) {
+        if (wave == 0) {
+            lds_double* D = S + ch_blk(b, b);
+            if (b > 0) {  // the last product of this sub-block, then its factor
+                const dmfma4 x = lds_load4(S + ch_blk(b, b - 1) + at);
+                lds_store4(D + at, mfma16(x, -x, lds_load4(D + at)));
+            }
+            // lane n (and its copies n + 16 g) holds row n of the sub-block and column n of
+            // the inverse
+            double rw[16], z[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                rw[j] = D[ch_at(n, j & 3) + (j >> 2)];
+                z[j] = j == n ? 1.0 : 0.0;
+            }
+            factor_pivots<0>(rw, z, n, bad);
+            if (lane < 16) {
+                double* Lg = Ld + (size_t)(16 * b + n) * ld + 16 * b;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    if (j <= n) Lg[4 * (j & 3) + (j >> 2)] = rw[j];
+                    D[ch_at(j, n & 3) + (n >> 2)] = z[j];  // Z[j][n]
+                }
+            }
+            if (!last) {  // Z_b for the solve launch
+                int rb, cb;
+                z_home(b, rb, cb);
+                store4(Ld + (size_t)(16 * rb + n) * ld + 16 * cb + 4 * g, lds_load4(D + at));
+            }
+        } else if (b > 0) {
+            // products of sub-block column b - 1 with the rest of the block
+            const int q = nsb - b;  // rows and columns b .. nsb - 1, without (b, b)
+            for (int t = wave; t < q * (q + 1) / 2; t += CH_WAVES - 1) {
+                int tb = 0;
+                while ((tb + 1) * (tb + 2) / 2 <= t) ++tb;
+                const int cb = t - tb * (tb + 1) / 2;
+                lds_double* V = S + ch_blk(b + tb, b + cb) + at;
+                const dmfma4 xc = lds_load4(S + ch_blk(b + cb, b - 1) + at);
+                const dmfma4 xt = lds_load4(S + ch_blk(b + tb, b - 1) + at);
+                lds_store4(V, mfma16(xc, -xt, lds_load4(V)));
+            }
+        }
+        __syncthreads();
+        // the sub-blocks below the factored one
+        for (int mb = b + 1 + wave; mb < nsb; mb += CH_WAVES) {
+            lds_double* V = S + ch_blk(mb, b) + at;
+            const dmfma4 x = mfma16(lds_load4(S + ch_blk(b, b) + at), lds_load4(V),
+                                    dmfma4{0.0, 0.0, 0.0, 0.0});
+            lds_store4(V, x);
+            store4(Ld + (size_t)(16 * mb + n) * ld + 16 * b + 4 * g, x);
+        }
+        __syncthreads();
+    }
+    if (bad && threadIdx.x == 0) atomicOr(a.status, MCNEGF_FLAG_NOTSPD);
+    if (last && wave == 0) {  // the two bordered rows
+        const int row = a.Np + (n & 1);
+        dmfma4 y[CH_SB];
+#pragma unroll
+        for (int kb = 0; kb < CH_SB; ++kb) {
+            y[kb] = dmfma4{0.0, 0.0, 0.0, 0.0};
+            if (kb < nsb) {
+                y[kb] = a.J <= 1 ? aorig4(a, Pe, ve, row, c0 + 16 * kb, g)
+                                 : load4(Le + (size_t)row * ld + c0 + 16 * kb + 4 * g);
+                if (a.J & 1) {
+                    const double* xr = Le + (size_t)row * ld + c0 + 4 * g - CH_NB;
+                    const double* xc = Ld + (size_t)(16 * kb + n) * ld + 4 * g - CH_NB;
+                    dmfma4 acc = dmfma4{0.0, 0.0, 0.0, 0.0};
+                    for (int k = 0; k < CH_SB; ++k) acc = mfma16(load4(xc + 16 * k), load4(xr + 16 * k), acc);
+                    y[kb] -= acc;
+                }
+            }
+        }
+        panel_solve(S, y, nsb, n, g);
+#pragma unroll
+        for (int kb = 0; kb < CH_SB; ++kb)
+            if (kb < nsb && n < 2) store4(Le + (size_t)row * ld + c0 + 16 * kb + 4 * g, y[kb]);
+    }
+}
+
+// Work index of a workgroup: consecutive workgroups are dealt to the eight XCDs in turn, so
+// each XCD takes one contiguous eighth of the (energy, tile) list and its L2 serves the rows
+// that neighbouring tiles share.  The grid is 8 x ceil(total / 8).
+__device__ inline int xcd_contiguous(int total) {
+    return (blockIdx.x & 7) * ((total + 7) >> 3) + (blockIdx.x >> 3);
+}
+
+// Rows below a full panel: V L_JJ^{-T}, two 16-row tiles per wavefront at a time, `rows` times.
+// An odd panel (UPD) first takes the product with the previous panel's 128 columns: its rows
+// and the panel's come from L2, and V is read once instead of being written by a launch of its
+// own and read again.
+constexpr int CH_SOLVE_WAVES = 4;
+constexpr int CH_SOLVE_ROWS = 32 * CH_SOLVE_WAVES;  // rows per workgroup and pass
+
+template <bool UPD>
+__global__ void __launch_bounds__(64 * CH_SOLVE_WAVES, 2) cholesky_solve_kernel(CholArgs a) {
+    __shared__ double S_raw[CH_NBLK * 256];
+    lds_double* S = (lds_double*)S_raw;
+    const int idx = xcd_contiguous(a.nE * a.tiles);
+    if (idx >= a.nE * a.tiles) return;
+    const int e = idx / a.tiles, part = idx - e * a.tiles;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const int at = ch_at(n, g);
+    const int R = a.Np + 2;
+    const int64_t ld = a.ld;
+    const int c0 = a.J * CH_NB;
+    const double* Pe = a.P + (size_t)e * a.N * ld;
+    const double* ve = a.vec + (size_t)e * 4 * a.N;
+    double* Le = a.Lall + (size_t)e * R * ld;
+    const double* Ld = Le + (size_t)c0 * ld + c0;
+    for (int q = wave; q < CH_NBLK; q += CH_SOLVE_WAVES) {
+        int mb = 0;
+        while ((mb + 1) * (mb + 2) / 2 <= q) ++mb;
+        int kb = q - mb * (mb + 1) / 2;
+        if (kb == mb) z_home(mb, mb, kb);
+        lds_store4(S + q * 256 + at, load4(Ld + (size_t)(16 * mb + n) * ld + 16 * kb + 4 * g));
+    }
+    __syncthreads();
+    for (int t = 0; t < a.rows; ++t) {
+        const int row0 = c0 + CH_NB + 32 * ((part * a.rows + t) * CH_SOLVE_WAVES + wave);
+        if (row0 >= R) break;
+        dmfma4 y[2][CH_SB];
+        double* dst[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            dst[h] = Le + (size_t)min(row0 + 16 * h + n, R - 1) * ld + c0 + 4 * g;
+        if (UPD) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int kb = 0; kb < CH_SB; ++kb) y[h][kb] = dmfma4{0.0, 0.0, 0.0, 0.0};
+            const double* xc = Ld + (size_t)n * ld + 4 * g - CH_NB;
+            for (int k = 0; k < CH_SB; ++k) {
+                const dmfma4 x0 = load4(dst[0] - CH_NB + 16 * k);
+                const dmfma4 x1 = load4(dst[1] - CH_NB + 16 * k);
+#pragma unroll
+                for (int kb = 0; kb < CH_SB; ++kb) {
+                    const dmfma4 c = load4(xc + (size_t)(16 * kb) * ld + 16 * k);
+                    y[0][kb] = mfma16(c, x0, y[0][kb]);
+                    y[1][kb] = mfma16(c, x1, y[1][kb]);
+                }
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            __builtin_amdgcn_sched_barrier(0);  // one tile's entries of V at a time (registers)
+#pragma unroll
+            for (int kb = 0; kb < CH_SB; ++kb) {
+                const dmfma4 v = a.J <= 1 ? aorig4(a, Pe, ve, row0 + 16 * h + n, c0 + 16 * kb, g)
+                                          : load4(dst[h] + 16 * kb);
+                y[h][kb] = UPD ? v - y[h][kb] : v;
+            }
+            panel_solve(S, y[h], CH_SB, n, g);
+            if (row0 + 16 * h + n < R) {
+#pragma unroll
+                for (int kb = 0; kb < CH_SB; ++kb) store4(dst[h] + 16 * kb, y[h][kb]);
+            }
         }
     }
+}
+
+// Update: one workgroup per tile of 32 F x 32 F entries, four wavefronts of F x F
+// accumulators (16 F x 16 F entries) each.  A 16x16x4 product occupies a SIMD for 64 clocks,
+// so a 128 x 128 tile needs 16 KB of operands per 8 columns and 4096 clocks: bandwidth is not
+// short, latency is.  The 8-column steps are staged in LDS (double-buffered, one barrier per
+// step) from registers loaded four steps ahead; two workgroups share a CU.  In a step lane group g takes the
+// positions 2 g, 2 g + 1 of both operands (the same permutation of the contracted columns on
+// both sides); a staged row is 64 bytes, its 16-byte pieces swizzled by the row so that eight
+// rows spread over all banks.
+template <int F>
+__global__ void __launch_bounds__(256, F == 4 ? 2 : 4) cholesky_update_kernel(CholArgs a) {
+    constexpr int TS = 32 * F;  // tile side
+    __shared__ double X[2][2 * TS * 8];
+    const int idx = xcd_contiguous(a.nE * a.tiles);
+    if (idx >= a.nE * a.tiles) return;
+    const int e = idx / a.tiles;
+    int t = idx - e * a.tiles;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const int Np = a.Np, R = Np + 2;
+    const int64_t ld = a.ld;
+    const int c1 = (a.J + 1) * CH_NB;
+    const int wide = min(a.m * CH_NB, Np - c1);  // columns of the update
+    const int nct = (wide + TS - 1) / TS, nrt = (R - c1 + TS - 1) / TS;
+    // tiles in groups of eight tile columns, row by row within a group (tile row >= tile
+    // column): the tiles that run together share their rows
+    int g0 = 0, ct = 0, rt = 0;
+    for (; g0 < nct; g0 += 8) {
+        const int w = min(8, nct - g0);
+        // rows g0 .. g0 + w - 1 hold 1 .. w tiles, the rest w
+        const int tri = w * (w + 1) / 2;
+        const int cnt = tri + (nrt - g0 - w) * w;
+        if (t >= cnt) {
+            t -= cnt;
+            continue;
+        }
+        if (t < tri) {
+            int q = 0;
+            while ((q + 1) * (q + 2) / 2 <= t) ++q;
+            rt = g0 + q;
+            ct = g0 + t - q * (q + 1) / 2;
+        } else {
+            rt = g0 + w + (t - tri) / w;
+            ct = g0 + (t - tri) % w;
+        }
+        break;
+    }
+    const int i0 = c1 + rt * TS + (wave & 1) * 16 * F;   // this wavefront's rows
+    const int j0 = c1 + ct * TS + (wave >> 1) * 16 * F;  // and columns
+    // a wavefront above the diagonal or outside the matrix stages and multiplies for nothing
+    const bool on = i0 + 16 * F > j0 && i0 < R && j0 < c1 + wide;
+    double* Le = a.Lall + (size_t)e * R * ld;
+    // [row tile][column block].  The products are summed by themselves and subtracted once: added
+    // one by one to entries near 1 the small ones would be lost, always on the same side
+    dmfma4 acc[F][F];
+#pragma unroll
+    for (int tb = 0; tb < F; ++tb)
+#pragma unroll
+        for (int cb = 0; cb < F; ++cb) acc[tb][cb] = dmfma4{0.0, 0.0, 0.0, 0.0};
+    const int K = a.m * CH_NB;
+    const char* base = reinterpret_cast<const char*>(Le + (c1 - K));
+    // staging: thread (r, q) = (tid / 4, tid % 4) copies piece q of the tile's rows r + 64 u and
+    // (u >= F / 2) of its columns' rows; byte offsets of one energy's factor are below 2^32
+    const int sr = threadIdx.x >> 2, sq = threadIdx.x & 3;
+    uint32_t off[F];
+#pragma unroll
+    for (int u = 0; u < F; ++u) {
+        const int row = (u < F / 2 ? c1 + rt * TS + 64 * u : c1 + ct * TS + 64 * (u - F / 2)) + sr;
+        off[u] = (uint32_t)((size_t)min(row, R - 1) * ld * 8) + 16u * (sq ^ ((sr >> 2) & 3));
+    }
+    dvec2 s0[F], s1[F];
+    auto load = [&](dvec2 (&st)[F], int k) {
+        const char* b = base + (size_t)k * 64;
+#pragma unroll
+        for (int u = 0; u < F; ++u) st[u] = *reinterpret_cast<const dvec2*>(b + off[u]);
+    };
+    auto put = [&](const dvec2 (&st)[F], int buf) {
+#pragma unroll
+        for (int u = 0; u < F; ++u)
+            *reinterpret_cast<dvec2*>(&X[buf][(64 * u + sr) * 8 + 2 * sq]) = st[u];
+    };
+    const int piece = 2 * (g ^ ((n >> 2) & 3));
+    const int xi = ((wave & 1) * 16 * F + n) * 8 + piece;
+    const int xj = (TS + (wave >> 1) * 16 * F + n) * 8 + piece;
+    auto take = [&](dvec2 (&v)[2 * F], int buf) {
+#pragma unroll
+        for (int q = 0; q < F; ++q) {
+            v[q] = *reinterpret_cast<const dvec2*>(&X[buf][xi + 128 * q]);
+            v[F + q] = *reinterpret_cast<const dvec2*>(&X[buf][xj + 128 * q]);
+        }
+    };
+    auto mult = [&](const dvec2 (&v)[2 * F]) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int tb = 0; tb < F; ++tb)
+#pragma unroll
+                for (int cb = 0; cb < F; ++cb)
+                    acc[tb][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[F + cb][r], v[tb][r],
+                                                                       acc[tb][cb], 0, 0, 0);
+    };
+    // While step k is multiplied from registers, step k + 1 is read from its buffer, step k + 2
+    // written to the other one and step k + 4 loaded, so a wavefront has its next products
+    // ready when it leaves the barrier.  Loads past the end re-read the last step, unused.
+    // The scheduling barriers keep the memory accesses ahead of the products.
+    const int nk = K / 8;  // a multiple of 32
+    dvec2 fa[2 * F], fb[2 * F];
+    load(s0, 0);
+    load(s1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    put(s0, 0);
+    load(s0, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    put(s1, 1);
+    load(s1, 3);
+    __syncthreads();
+    take(fa, 0);
+    __syncthreads();
+    for (int k = 0; k < nk; k += 2) {
+        take(fb, 1);
+        put(s0, 0);
+        load(s0, min(k + 4, nk - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        mult(fa);
+        __syncthreads();
+        take(fa, 0);
+        put(s1, 1);
+        load(s1, min(k + 5, nk - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        mult(fb);
+        __syncthreads();
+    }
+    if (!on) return;
+    const bool first = a.J + 1 == a.m;
+    const double* Pe = a.P + (size_t)e * a.N * ld;
+    const double* ve = a.vec + (size_t)e * 4 * a.N;
+#pragma unroll
+    for (int tb = 0; tb < F; ++tb)
+#pragma unroll
+        for (int cb = 0; cb < F; ++cb) {
+            const int row = i0 + 16 * tb + n, col = j0 + 16 * cb;
+            if (row < R && col < Np) {
+                double* at = Le + (size_t)row * ld + col + 4 * g;
+                const dmfma4 v = first ? aorig4(a, Pe, ve, row, col, g) : load4(at);
+                store4(at, v - acc[tb][cb]);
+            }
+        }
 }
 
 // T_k = T_qp + (row Np of L) . (row Np + 1 of L) after a factorization in several launches
@@ -780,6 +885,45 @@ hipError_t launch_current_out(const mcnegf_kernel& k, double* d_I_sigma, hipStre
     return hipGetLastError();
 }
 
+// The factorization's launches, under one timer record.
+static hipError_t factorize(CholArgs a, int cus, hipStream_t s) {
+    MCNEGF_TIMED("cholesky_kernel", s);
+    const int R = a.Np + 2;
+    const int nJ = (a.Np + CH_NB - 1) / CH_NB;
+    auto grid = [&] { return dim3(8u * (unsigned)(((int64_t)a.nE * a.tiles + 7) / 8)); };
+    hipError_t err;
+    for (int J = 0; J < nJ; ++J) {
+        a.J = J;
+        hipLaunchKernelGGL(cholesky_factor_kernel, dim3(a.nE), dim3(64 * CH_WAVES), 0, s, a);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+        if (J + 1 == nJ) break;
+        // solve: at most about two workgroups per CU (each loads the whole panel block)
+        const int below = (R - (J + 1) * CH_NB + CH_SOLVE_ROWS - 1) / CH_SOLVE_ROWS;
+        const int per = std::min(std::max(2 * cus / a.nE, 1), below);
+        a.rows = (below + per - 1) / per;
+        a.tiles = (below + a.rows - 1) / a.rows;
+        const dim3 block(64 * CH_SOLVE_WAVES);
+        if (J & 1) hipLaunchKernelGGL(cholesky_solve_kernel<true>, grid(), block, 0, s, a);
+        else hipLaunchKernelGGL(cholesky_solve_kernel<false>, grid(), block, 0, s, a);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+        if ((J & 1) == 0) continue;
+        // update of the next m panels: 128 x 128 tiles while they fill the chip, else 64 x 64
+        a.m = (J + 1) & -(J + 1);
+        const int c1 = (J + 1) * CH_NB;
+        const int wide = std::min(a.m * CH_NB, a.Np - c1);
+        auto tiles = [&](int side) {
+            const int nct = (wide + side - 1) / side, nrt = (R - c1 + side - 1) / side;
+            return nct * (nct + 1) / 2 + (nrt - nct) * nct;
+        };
+        const bool big = (int64_t)tiles(128) * a.nE >= cus;
+        a.tiles = tiles(big ? 128 : 64);
+        if (big) hipLaunchKernelGGL(cholesky_update_kernel<4>, grid(), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(cholesky_update_kernel<2>, grid(), dim3(256), 0, s, a);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_direct_current(const mcnegf_kernel& k, uint32_t inject_lead,
                                  const double* weights, double* T, double* sigmaT, hipStream_t s) {
     const int N = k.N;
@@ -802,51 +946,18 @@ hipError_t launch_direct_current(const mcnegf_kernel& k, uint32_t inject_lead,
     a.Np = (int)k.p_pitch;
     a.ld = k.p_pitch;
     a.inject_lead = inject_lead;
-    const int nJ = (a.Np + CH_NB - 1) / CH_NB;
-    // One workgroup (one CU) per energy.  When the energies leave CUs idle and the matrix is
-    // large, split each energy over several workgroups, one launch per block column (the
-    // launch boundary orders the block columns; no cross-workgroup waits).
+    a.nE = k.nE;
     int dev = 0, cus = 0;
     if ((err = hipGetDevice(&dev)) != hipSuccess) return err;
     if ((err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) !=
         hipSuccess)
         return err;
-    // Each workgroup of an energy forms the diagonal factor itself, so keep at least two
-    // super-tiles of the first block column per workgroup (four workgroups at any size).
-    const int nst = (a.Np - CH_NB + CH_ROWS - 1) / CH_ROWS;
-    const int cap = (nst + 1) / 2 > 4 ? (nst + 1) / 2 : 4;
-    int nsplit = cus / (k.nE > 0 ? k.nE : 1);
-    nsplit = nsplit > cap ? cap : nsplit;
-    if (a.Np < 1024 || nJ < 4) nsplit = 1;
-    if (nsplit <= 1) {
-        a.J0 = 0;
-        a.J1 = nJ;
-        a.nsplit = 1;
-        a.single = true;
-        {
-            MCNEGF_TIMED("cholesky_kernel", s);
-            hipLaunchKernelGGL(cholesky_kernel, dim3(k.nE), dim3(64 * CH_WAVES), 0, s, a);
-        }
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-    } else {
-        a.nsplit = nsplit;
-        a.single = false;
-        for (int J = 0; J < nJ; ++J) {
-            a.J0 = J;
-            a.J1 = J + 1;
-            {
-                MCNEGF_TIMED("cholesky_kernel", s);
-                hipLaunchKernelGGL(cholesky_kernel, dim3(k.nE * nsplit), dim3(64 * CH_WAVES), 0, s,
-                                   a);
-            }
-            if ((err = hipGetLastError()) != hipSuccess) return err;
-        }
-        {
-            MCNEGF_TIMED("direct_dot_kernel", s);
-            hipLaunchKernelGGL(direct_dot_kernel, dim3(k.nE), dim3(256), 0, s, a);
-        }
-        if ((err = hipGetLastError()) != hipSuccess) return err;
+    if ((err = factorize(a, cus, s)) != hipSuccess) return err;
+    {
+        MCNEGF_TIMED("direct_dot_kernel", s);
+        hipLaunchKernelGGL(direct_dot_kernel, dim3(k.nE), dim3(256), 0, s, a);
     }
+    if ((err = hipGetLastError()) != hipSuccess) return err;
     {
         MCNEGF_TIMED("current_sum_kernel", s);
         hipLaunchKernelGGL(current_sum_kernel, dim3(1), dim3(256), 0, s, T, sigmaT, weights, k.nE,

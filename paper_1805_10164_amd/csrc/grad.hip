@@ -38,8 +38,8 @@ __device__ inline double readlane_dbl(double v, int lane) {
 }
 
 // L^T xt = y and L^T lt = z with L the Cholesky factor of the bordered scaled probe system
-// (lower part, columns of each 16-block stored permuted) and y, z its bordered rows Np and
-// Np + 1; then x = s xt and lambda = s lt (s_j = M_jj^{-1/2}, vector slot 3).  One workgroup
+// (lower part, columns of each 16-block stored permuted, logical row and column i being site
+// perm16(i)) and y, z its bordered rows Np and Np + 1; then x = s xt and lambda = s lt (s_j = M_jj^{-1/2}, vector slot 3).  One workgroup
 // of 1024 threads per energy, right-looking over block rows of 64 from the last one down:
 //   solve  L_II^T x_I = r_I       (diagonal block staged in LDS, one wavefront, lane per row)
 //   update r_j -= sum_{i in I} L_ij x_i   for every j < 64 I
@@ -103,9 +103,10 @@ __global__ void __launch_bounds__(BSV_THREADS) backsolve_kernel(const double* __
             if (m < wI) {
                 xI[0][m] = ax;
                 xI[1][m] = al;
-                if (c0 + m < N) {
-                    xo[c0 + m] = s[c0 + m] * ax;
-                    xo[ld + c0 + m] = s[c0 + m] * al;
+                const int site = c0 + pm;  // the factor takes the sites in stored order
+                if (site < N) {
+                    xo[site] = s[site] * ax;
+                    xo[ld + site] = s[site] * al;
                 }
             }
         }
