@@ -1,44 +1,44 @@
 // All blocks of G^r from the RGF blocks, streamed straight into the walker's weights.
 //
 // For a column l (slice of the column), the blocks of G obey (E - H - Sigma) G = I with
-// off-diagonal blocks t I, which gives
-//   above the diagonal  G_{k,l} = -t gL_k G_{k+1,l}   (k < l),
-//   below the diagonal  G_{k,l} = -t gR_k G_{k-1,l}   (k > l),
-// starting from the diagonal block G_{l,l}.  Each lane owns one column j of G (a workgroup
-// is one wavefront owning 64 consecutive columns) and keeps its W-vector G_{k, j} in
-// registers while the wavefront sweeps k down and then up the wire; the W x W factors gL_k,
+// off-diagonal blocks t I, which below the diagonal gives
+//   G_{k,l} = -t gR_k G_{k-1,l}   (k > l),
+// starting from the diagonal block G_{l,l}.  G is complex symmetric (real H, symmetric lead
+// self-energies), so the blocks above the diagonal are their transposes: only the lower half is
+// computed, and every entry below the diagonal blocks is stored twice.  Each lane owns one
+// column j of G (a workgroup is one wavefront owning 64 consecutive columns) and keeps its
+// W-vector G_{k, j} in registers while the wavefront sweeps k down the wire; the W x W factors
 // gR_k are the same for every lane: the wavefront stages them in LDS one slice ahead
-// (double-buffered) and every lane reads the same address (a broadcast), which keeps the
-// block operands off the scalar path and the texture units.  Nothing of G is written except
+// (double-buffered) and every lane reads the same address (a broadcast), which keeps the block
+// operands off the scalar path and the texture units.  Nothing of G is written except
 //   P[i][j]  = |G_ij|^2                      (probe-to-probe weights, step 6', Eq. (75)),
 //   wL[j]    = <psi_j|Gamma_L|psi_j>, wR[j]  (psi_j = G|j>, exit weights, Eq. (76)),
 //   corner   = G_{L-1,0} and G_{0,L-1}       (lead-to-lead transmissions).
-// Rows of P are written by 64 lanes at consecutive columns (coalesced 512-byte segments).
+// Rows of P are written by 64 lanes at consecutive columns (coalesced 512-byte segments), the
+// transposed entries through LDS by whole aligned 128-byte lines (W = 10: 0.79 ms by 64-byte
+// sectors, 0.99 ms by the 80 bytes of a slice).
+// wL[j] needs G_{0,j}, i.e. row j of the columns of slice 0 (exit_left_chain; on the matrix
+// cores the first workgroup of an energy forms them from its columns as it passes).
+// Half the block products and one sweep instead of two: 0.75 -> 0.54 ms at W = 10, N = 1000,
+// 256 energies (3.8 TB/s of |G|^2 written), 2.82 -> 2.32 ms over six W = 8 wires.  With few
+// wavefronts the chain of slices bounds it (W = 7, 61 slices, 37 energies: 0.10 ms before and
+// after).
 // The block products run on the FP64 VALU: the operands live in registers and LDS, and
 // gfx950's FP64 matrix-core rate equals its FP64 FMA rate, so padding W up to a 16x16x4 MFMA
 // shape would only add work.  Up to W = 24 the column and the product fit the register file;
 // at W = 32 a few values spill.
+#include <type_traits>
+
 #include "common.h"
 
 namespace mcnegf {
 
-template <int W>
-__device__ inline double quad_form(const double2 (&v)[W], const double* __restrict__ gm) {
-    double acc = 0.0;
-#pragma unroll
-    for (int a = 0; a < W; ++a) {
-#pragma unroll
-        for (int b = 0; b < W; ++b)
-            acc = fma(gm[a * W + b], v[a].x * v[b].x + v[a].y * v[b].y, acc);
-    }
-    return acc;
-}
-
 typedef __attribute__((address_space(3))) double lds_double;
 
-// v <- mt * M v for a W x W complex block M staged in LDS as (re, im) pairs, row-major.
+// v <- mt * M v for a W x W complex block M staged in LDS as (re, im) pairs, row-major, in the
+// lanes where on is set.
 template <int W>
-__device__ inline void block_matvec(double2 (&v)[W], const lds_double* M, double mt) {
+__device__ inline void block_matvec(double2 (&v)[W], const lds_double* M, double mt, bool on) {
     double2 nv[W];
 #pragma unroll
     for (int y = 0; y < W; ++y) {
@@ -46,27 +46,107 @@ __device__ inline void block_matvec(double2 (&v)[W], const lds_double* M, double
 #pragma unroll
         for (int x = 0; x < W; ++x) cfma(acc, cmk(M[2 * (y * W + x)], M[2 * (y * W + x) + 1]), v[x]);
         nv[y] = cscale(acc, mt);
+        // keeps the products here: sunk into a branch on `on`, they would leave the whole block
+        // in registers (affordable, and faster with few wavefronts, for narrow blocks)
+        if constexpr (W > 5) asm volatile("" : "+v"(nv[y].x), "+v"(nv[y].y));
     }
 #pragma unroll
-    for (int y = 0; y < W; ++y) v[y] = nv[y];
+    for (int y = 0; y < W; ++y) v[y] = cmk(on ? nv[y].x : v[y].x, on ? nv[y].y : v[y].y);
 }
 
-// The NT threads copy the W x W block src into the LDS buffer dst (thread tid).
-template <int W, int NT = 64>
-__device__ inline void stage_block(lds_double* dst, const double2* __restrict__ src, int tid) {
+// A W x W block on its way from memory to LDS by NT threads: loaded into registers one slice
+// before it is written to LDS, so that the wait for the loads does not include the stores of
+// the slice in between (the memory counter retires them in order).
+template <int W, int NT>
+struct StagedBlock {
+    static constexpr int n = (W * W + NT - 1) / NT;
+    typedef double dvec2 __attribute__((ext_vector_type(2)));
+    dvec2 r[n];
+    __device__ inline void load(const double2* __restrict__ src, int tid) {
 #pragma unroll
-    for (int i = tid; i < W * W; i += NT) {
-        const double2 v = src[i];
-        dst[2 * i] = v.x;
-        dst[2 * i + 1] = v.y;
+        for (int i = 0; i < n; ++i)
+            r[i] = reinterpret_cast<const dvec2*>(src)[min(tid + i * NT, W * W - 1)];
+    }
+    __device__ inline void write(lds_double* dst, int tid) const {
+#pragma unroll
+        for (int i = 0; i < n; ++i)
+            if (W * W % NT == 0 || tid + i * NT < W * W) {
+                dst[2 * (tid + i * NT)] = r[i].x;
+                dst[2 * (tid + i * NT) + 1] = r[i].y;
+            }
+    }
+};
+
+// Exit weights into L of one energy, on one wavefront: the columns of slice 0, X = G_{k,0} (W x W
+// in LDS, lanes over its entries), go down the wire by themselves, and row y of slice k weighs
+// sum_a Re conj(X_ya) (Gamma X^T)_ay.  As a chain of its own it stays off the wavefront that
+// stores those columns (the longest one).
+template <int W>
+__device__ inline void exit_left_chain(lds_double* Ms, lds_double* X,
+                                       const double2* __restrict__ gRe,
+                                       const double2* __restrict__ Gde,
+                                       const double* __restrict__ gme, int L, double mt,
+                                       double* __restrict__ wLe) {
+    constexpr int BS = 2 * W * W;
+    constexpr int PN = (W * W + 63) / 64;  // entries per lane
+    constexpr int UW = W <= 16 ? W : 4;    // unrolling of the inner products
+    lds_double* terms = X + 2 * W * W;
+    lds_double* Gs = X + 3 * W * W;  // (W <= 16; wider blocks read Gamma from memory)
+    const int lane = threadIdx.x;
+    int y[PN], a[PN];
+#pragma unroll
+    for (int i = 0; i < PN; ++i) {
+        const int p = min(lane + 64 * i, W * W - 1);
+        y[i] = p / W;
+        a[i] = p - y[i] * W;
+        const double2 x = Gde[p];
+        X[2 * p] = x.x;
+        X[2 * p + 1] = x.y;
+        if constexpr (W <= 16) Gs[p] = gme[p];
+    }
+    StagedBlock<W, 64> st;
+    st.load(gRe + (size_t)min(1, L - 1) * W * W, lane);
+    for (int k = 0; k < L; ++k) {
+        lds_double* M = Ms + (k & 1) * BS;
+        st.write(M, lane);  // block k + 1
+        st.load(gRe + (size_t)min(k + 2, L - 1) * W * W, lane);
+        __syncthreads();  // one wavefront: orders the LDS accesses
+        double2 nx[PN];
+#pragma unroll
+        for (int i = 0; i < PN; ++i) {
+            double2 u = cmk(0.0, 0.0), acc = cmk(0.0, 0.0);
+            const lds_double* xr = X + 2 * (y[i] * W);
+            const lds_double* xc = X + 2 * a[i];
+            const lds_double* m = M + 2 * (y[i] * W);
+#pragma unroll UW
+            for (int b = 0; b < W; ++b) {
+                const double gab = W <= 16 ? Gs[a[i] * W + b] : gme[a[i] * W + b];
+                u = cadd(u, cscale(cmk(xr[2 * b], xr[2 * b + 1]), gab));
+                cfma(acc, cmk(m[2 * b], m[2 * b + 1]), cmk(xc[2 * b * W], xc[2 * b * W + 1]));
+            }
+            terms[y[i] * W + a[i]] = fma(xr[2 * a[i]], u.x, xr[2 * a[i] + 1] * u.y);
+            nx[i] = cscale(acc, mt);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PN; ++i) {
+            X[2 * (y[i] * W + a[i])] = nx[i].x;
+            X[2 * (y[i] * W + a[i]) + 1] = nx[i].y;
+        }
+        if (lane < W) {
+            double sum = 0.0;
+#pragma unroll UW
+            for (int b = 0; b < W; ++b) sum += terms[lane * W + b];
+            wLe[k * W + lane] = sum;
+        }
+        __syncthreads();
     }
 }
 
 // STORE_G: write the complex blocks of G (row-major, pitch ldG, Gc) instead of |G_ij|^2,
 // the exit weights and the corners.
 template <int W, bool STORE_G>
-__global__ void __launch_bounds__(64) fullinv_kernel(const double2* __restrict__ gL,
-                                                      const double2* __restrict__ gR,
+__global__ void __launch_bounds__(64) fullinv_kernel(const double2* __restrict__ gR,
                                                       const double2* __restrict__ Gd,
                                                       const double* __restrict__ gam_lead,
                                                       int L, double t, int64_t ldP,
@@ -78,106 +158,113 @@ __global__ void __launch_bounds__(64) fullinv_kernel(const double2* __restrict__
                                                       int nE) {
     const int N = W * L;
     // XCD-aware order: workgroups are dealt to the eight XCDs in turn (workgroup b on XCD
-    // b % 8); every column tile of energy e runs on XCD e % 8, whose L2 then fetches that
-    // energy's RGF blocks once for all its tiles
-    const int tiles = (N + 63) / 64;
+    // b % 8); every column tile of energy e runs on XCD e % 8, whose L2 then serves that
+    // energy's RGF blocks to all its tiles.  Tile by tile over the energies, so that the long
+    // tiles (the first columns) start first and are dealt evenly to the CUs.
+    const int per_xcd = (nE + 7) / 8;
     const int xcd = blockIdx.x & 7, jb = blockIdx.x >> 3;
-    const int e = xcd + 8 * (jb / tiles);
+    const int e = xcd + 8 * (jb % per_xcd);
     if (e >= nE) return;  // padding of the last round (whole workgroup)
     const int lane = threadIdx.x;
-    const int wave_first = (jb % tiles) * 64;
+    // index 0 is the chain of the exit weights into L, index t + 1 the t-th 64 columns
+    const int tile = jb / per_xcd - (STORE_G ? 0 : 1);
+    const int wave_first = tile * 64;
     const int col = wave_first + lane;
     const bool valid = col < N;
     const int colc = valid ? col : N - 1;
     const int l = colc / W;
     const int y0 = colc - l * W;
-    const int wave_last = min(wave_first + 63, N - 1);
     const int kmin = wave_first / W;
-    const int kmax = wave_last / W;
     const size_t eb = (size_t)e * L * W * W;
-    const double2* gLe = gL + eb;
     const double2* gRe = gR + eb;
     const double2* Gde = Gd + eb;
     const double* gme = gam_lead + (size_t)e * W * W;
-    double* Pe = P + (size_t)e * N * ldP;
-    double2* cRL = corner + (size_t)e * 2 * W * W;
-    double2* cLR = cRL + W * W;
     const double mt = -t;
     constexpr int BS = 2 * W * W;  // doubles per staged block
     __shared__ double Ms_raw[2 * BS];
     lds_double* Ms = (lds_double*)Ms_raw;
-
+    // what is stored per entry, and a ring of rows whose transposed entries wait until FR
+    // aligned rows (whole 128-byte lines of the transposed row) are there
+    typedef typename std::conditional<STORE_G, double2, double>::type Entry;
+    constexpr int FR = 128 / sizeof(Entry);
+    constexpr int RB = FR + W - 1;
+    __shared__ Entry Tr[RB][65];
+    if constexpr (!STORE_G) {
+        static_assert((W <= 16 ? 4 : 3) * W * W <= RB * 65, "the chain's blocks fit the ring");
+        if (tile < 0) {
+            lds_double* X = (lds_double*)&Tr[0][0];
+            exit_left_chain<W>(Ms, X, gRe, Gde, gme, L, mt, wL + (size_t)e * N);
+            return;  // the whole workgroup
+        }
+    }
+    Entry* Oe = STORE_G ? (Entry*)Gc + (size_t)e * N * ldG : (Entry*)P + (size_t)e * N * ldP;
+    const int64_t ldO = STORE_G ? ldG : ldP;
+    const int tc = lane / FR, tr = lane % FR;  // transposed store: column and row of a pass
+    int pending = (kmin * W) & ~(FR - 1);      // first row not stored transposed
+    // from this row on every column of the tile is stored transposed (none: ragged last tile)
+    const int below = wave_first + 64 <= N ? ((wave_first + 63) / W + 1) * W : N;
+    // the column of the diagonal block, kept until the sweep has passed its slice
     double2 v[W];
-    // ---- downward: k = l, l+1, ..., L-1 -------------------------------------------------
 #pragma unroll
-    for (int y = 0; y < W; ++y) v[y] = cmk(0.0, 0.0);
-    stage_block<W>(Ms, gRe + (size_t)kmin * W * W, lane);
+    for (int y = 0; y < W; ++y) v[y] = Gde[((size_t)l * W + y) * W + y0];
+    StagedBlock<W, 64> st;  // block k + 1 at the top of slice k (the last one again past the end)
+    st.load(gRe + (size_t)kmin * W * W, lane);
+    st.write(Ms, lane);
+    st.load(gRe + (size_t)min(kmin + 1, L - 1) * W * W, lane);
     for (int k = kmin; k < L; ++k) {
         __syncthreads();  // block k staged; the other buffer is free
         const int b = (k - kmin) & 1;
-        if (k + 1 < L) stage_block<W>(Ms + (b ^ 1) * BS, gRe + (size_t)(k + 1) * W * W, lane);
-        block_matvec<W>(v, Ms + b * BS, mt);
-        if (k == l) {
+        st.write(Ms + (b ^ 1) * BS, lane);
+        st.load(gRe + (size_t)min(k + 2, L - 1) * W * W, lane);
+        block_matvec<W>(v, Ms + b * BS, mt, k > l);
+        const int base = (k * W) % RB;
 #pragma unroll
-            for (int y = 0; y < W; ++y) v[y] = Gde[(size_t)k * W * W + y * W + y0];
+        for (int y = 0; y < W; ++y) {
+            Entry o;
+            if constexpr (STORE_G) o = v[y];
+            else o = cabs2(v[y]);
+            if (valid && k >= l) Oe[(size_t)(k * W + y) * ldO + col] = o;
+            Tr[base + y < RB ? base + y : base + y - RB][lane] = o;
         }
-        if (k < l) {
-#pragma unroll
-            for (int y = 0; y < W; ++y) v[y] = cmk(0.0, 0.0);
-        }
-        if (valid && k >= l) {
-            if (STORE_G) {
-                double2* Ge = Gc + (size_t)e * N * ldG;
-#pragma unroll
-                for (int y = 0; y < W; ++y) Ge[(size_t)(k * W + y) * ldG + col] = v[y];
+        __syncthreads();  // one wavefront: orders the LDS accesses
+        const int end = (k + 1) * W;
+        while (pending + FR <= end || (k == L - 1 && pending < end)) {
+            const int r = pending + tr;
+            const int at = pending % RB + tr;
+            const Entry* row = Tr[at < RB ? at : at - RB];
+            Entry* dst = Oe + (size_t)(wave_first + tc) * ldO + r;
+            if (pending >= below && pending + FR <= end) {  // every entry is stored
+#pragma unroll 8
+                for (int c = 0; c < 64; c += 64 / FR) dst[(size_t)c * ldO] = row[c + tc];
             } else {
-#pragma unroll
-                for (int y = 0; y < W; ++y) Pe[(size_t)(k * W + y) * ldP + col] = cabs2(v[y]);
+#pragma unroll 1
+                for (int c = 0; c < 64; c += 64 / FR) {
+                    const int j = wave_first + c + tc;
+                    if (j < N && r < end && r >= (j / W + 1) * W) dst[(size_t)c * ldO] = row[c + tc];
+                }
             }
+            pending += FR;
         }
     }
-    // k = L-1 now: exit weight into R and, for columns of slice 0, the corner G_{L-1,0}.
-    if (valid && !STORE_G) {
-        wR[(size_t)e * N + col] = quad_form<W>(v, gme);
+    if (STORE_G) return;
+    // k = L-1 now: exit weight into R and, for the columns of slice 0, the corner blocks
+    if (valid) {
+        double acc = 0.0;
+#pragma unroll
+        for (int a = 0; a < W; ++a) {
+#pragma unroll
+            for (int bb = 0; bb < W; ++bb)
+                acc = fma(gme[a * W + bb], v[a].x * v[bb].x + v[a].y * v[bb].y, acc);
+        }
+        wR[(size_t)e * N + col] = acc;
         if (l == 0) {
+            double2* cRL = corner + (size_t)e * 2 * W * W;
+            double2* cLR = cRL + W * W;
 #pragma unroll
-            for (int y = 0; y < W; ++y) cRL[y * W + y0] = v[y];
-        }
-    }
-    // ---- upward: k = l, l-1, ..., 0 ------------------------------------------------------
-#pragma unroll
-    for (int y = 0; y < W; ++y) v[y] = cmk(0.0, 0.0);
-    __syncthreads();  // downward reads done
-    stage_block<W>(Ms, gLe + (size_t)kmax * W * W, lane);
-    for (int k = kmax; k >= 0; --k) {
-        __syncthreads();
-        const int b = (kmax - k) & 1;
-        if (k > 0) stage_block<W>(Ms + (b ^ 1) * BS, gLe + (size_t)(k - 1) * W * W, lane);
-        block_matvec<W>(v, Ms + b * BS, mt);
-        if (k == l) {
-#pragma unroll
-            for (int y = 0; y < W; ++y) v[y] = Gde[(size_t)k * W * W + y * W + y0];
-        }
-        if (k > l) {
-#pragma unroll
-            for (int y = 0; y < W; ++y) v[y] = cmk(0.0, 0.0);
-        }
-        if (valid && k < l) {
-            if (STORE_G) {
-                double2* Ge = Gc + (size_t)e * N * ldG;
-#pragma unroll
-                for (int y = 0; y < W; ++y) Ge[(size_t)(k * W + y) * ldG + col] = v[y];
-            } else {
-#pragma unroll
-                for (int y = 0; y < W; ++y) Pe[(size_t)(k * W + y) * ldP + col] = cabs2(v[y]);
+            for (int y = 0; y < W; ++y) {
+                cRL[y * W + y0] = v[y];
+                cLR[y0 * W + y] = v[y];
             }
-        }
-    }
-    if (valid && !STORE_G) {
-        wL[(size_t)e * N + col] = quad_form<W>(v, gme);
-        if (l == L - 1) {
-#pragma unroll
-            for (int y = 0; y < W; ++y) cLR[y * W + y0] = v[y];
         }
     }
 }
@@ -185,12 +272,11 @@ __global__ void __launch_bounds__(64) fullinv_kernel(const double2* __restrict__
 template <int W, bool STORE_G>
 static hipError_t launch_fullinv_w(const mcnegf_kernel& k, double2* Gc, int64_t ldG,
                                    hipStream_t s) {
-    const unsigned tiles = (unsigned)((k.N + 63) / 64);
+    const unsigned tiles = (unsigned)((k.N + 63) / 64) + (STORE_G ? 0 : 1);  // and the chain
     dim3 grid(8u * tiles * (unsigned)((k.nE + 7) / 8));
     {
         MCNEGF_TIMED(STORE_G ? "fullinv_store_g_kernel" : "fullinv_kernel", s);
         hipLaunchKernelGGL((fullinv_kernel<W, STORE_G>), grid, dim3(64), 0, s,
-                           reinterpret_cast<const double2*>(k.gL),
                            reinterpret_cast<const double2*>(k.gR),
                            reinterpret_cast<const double2*>(k.Gd), k.gam_lead, k.L, k.t, k.p_pitch,
                            k.P, k.wL, k.wR, reinterpret_cast<double2*>(k.corner), Gc, ldG,
@@ -201,17 +287,19 @@ static hipError_t launch_fullinv_w(const mcnegf_kernel& k, double2* Gc, int64_t 
 
 // ---- W = 16 and W = 32 on FP64 matrix cores ----------------------------------------------
 //
-// The same sweeps, with the block products on v_mfma_f64_16x16x4f64 (no padding at these
+// The same sweep, with the block products on v_mfma_f64_16x16x4f64 (no padding at these
 // widths).  A workgroup of NW wavefronts shares one double-buffered staged block (so the LDS of
 // a workgroup does not limit the wavefronts a CU holds) and sweeps from its first column's
-// slice (downward) and its last column's slice (upward); a wavefront's columns stay zero until
-// their own slice.  A wavefront owns TC tiles of 16 consecutive columns; lane (n, g) = (l % 16, l / 16)
+// slice; a wavefront's columns hold their diagonal block's column until it is passed.  A
+// wavefront owns TC tiles of 16 consecutive columns; lane (n, g) = (l % 16, l / 16)
 // holds, for tile t and row tile rt, the rows 16 rt + 4 r + g (r = 0..3) of column n, which is
 // both the accumulator layout of the product (item r of lane n + 16 g is row 4 r + g) and the
 // B-operand layout of the next product (K-step s takes rows 4 s + g from lane n + 16 g), so the
 // columns stay in registers from slice to slice.  The A operand of K-step s and row tile rt,
 // lane (m, g): (-t) M[16 rt + m][4 s + g], read from the LDS-staged block.  A complex product
 // is four real products (re re, -im im into the real part; re im, im re into the imaginary).
+// With the lower half only: W = 16, N = 3200, 128 energies 5.33 -> 2.36 ms (|G|^2; 4.5 TB/s
+// written) and 6.97 -> 4.96 ms (complex G); W = 32, N = 16000, 8 energies 11.2 -> 7.5 ms.
 typedef double dmfma4 __attribute__((ext_vector_type(4)));
 typedef float fmfma4 __attribute__((ext_vector_type(4)));
 
@@ -235,12 +323,33 @@ __device__ inline int tile_row(int r, int g) {
     return sizeof(T) == 8 ? 4 * r + g : 4 * g + r;
 }
 
+// x[r] of lane group g becomes x[g] of lane group r (a 4 x 4 transpose across the groups of 16
+// lanes): exchange half wavefronts between items 0, 2 and 1, 3, then neighbouring groups
+// between items 0, 1 and 2, 3.  Every lane must be active.
+__device__ inline void swap_halves(double& a, double& b) {
+    auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double(hi[0], lo[0]);
+    b = __hiloint2double(hi[1], lo[1]);
+}
+__device__ inline void swap_groups(double& a, double& b) {
+    auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double(hi[0], lo[0]);
+    b = __hiloint2double(hi[1], lo[1]);
+}
+__device__ inline void transpose_groups(double (&x)[4]) {
+    swap_halves(x[0], x[2]);
+    swap_halves(x[1], x[3]);
+    swap_groups(x[0], x[1]);
+    swap_groups(x[2], x[3]);
+}
+
 // T = double: FP64 products throughout.  T = float (a build with FP32 block products): the
 // column state and the products are FP32 (the staged FP64 blocks are rounded as they are
 // read), |G|^2, the exit weights and the corners are formed from the FP32 state in FP64.
 template <int W, int TC, int NW, bool STORE_G, typename T = double>
-__global__ void __launch_bounds__(64 * NW) fullinv_mfma_kernel(const double2* __restrict__ gL,
-                                                          const double2* __restrict__ gR,
+__global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2* __restrict__ gR,
                                                           const double2* __restrict__ Gd,
                                                           const double* __restrict__ gam_lead,
                                                           int L, double t, int64_t ldP,
@@ -254,23 +363,25 @@ __global__ void __launch_bounds__(64 * NW) fullinv_mfma_kernel(const double2* __
     constexpr int BS = 2 * W * W;
     __shared__ double Ms_raw[2 * BS];
     lds_double* Ms = (lds_double*)Ms_raw;
+    // (first workgroup of an energy) Gamma and, double-buffered, the columns of slice 0 at the
+    // current slice, [column][row]
+    constexpr int XN = STORE_G ? 1 : W * W;
+    __shared__ double Gs[XN];
+    __shared__ double2 X[2][XN];
     const int N = W * L;
-    const int e = blockIdx.y;
+    const int e = blockIdx.x;  // tile by tile over the energies: the long tiles start first
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
-    const int cg0 = blockIdx.x * NW * 16 * TC;  // the workgroup's first column
+    const int cg0 = blockIdx.y * NW * 16 * TC;  // the workgroup's first column
     const int c0 = cg0 + (tid >> 6) * 16 * TC;  // this wavefront's first column
     const int kmin = cg0 / W;
-    const int kmax = (min(cg0 + NW * 16 * TC, N) - 1) / W;
+    const bool slice0 = !STORE_G && cg0 == 0;  // its first wavefront holds the columns of slice 0
     const size_t eb = (size_t)e * L * W * W;
-    const double2* gLe = gL + eb;
     const double2* gRe = gR + eb;
     const double2* Gde = Gd + eb;
     const double* gme = gam_lead + (size_t)e * W * W;
     double* Pe = P + (size_t)e * N * ldP;
-    double2* cRL = corner + (size_t)e * 2 * W * W;
-    double2* cLR = cRL + W * W;
     double2* Ge = Gc + (size_t)e * N * ldG;
     const double mt = -t;
 
@@ -287,8 +398,9 @@ __global__ void __launch_bounds__(64 * NW) fullinv_mfma_kernel(const double2* __
     typedef typename Mfma4<T>::type acc4;
     T vr[TC][RT][4], vi[TC][RT][4];
 
-    // one slice: v <- (-t) M v with M the block staged at buf
-    auto product = [&](const lds_double* buf) {
+    // one slice: v <- (-t) M v with M the block staged at buf, for the columns the sweep has
+    // passed (the others keep their diagonal block's column)
+    auto product = [&](const lds_double* buf, int k) {
         acc4 cr[TC][RT], ci[TC][RT];
 #pragma unroll
         for (int tc = 0; tc < TC; ++tc)
@@ -324,46 +436,64 @@ __global__ void __launch_bounds__(64 * NW) fullinv_mfma_kernel(const double2* __
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    vr[tc][rt][r] = cr[tc][rt][r];
-                    vi[tc][rt][r] = ci[tc][rt][r];
+                    vr[tc][rt][r] = k > l[tc] ? cr[tc][rt][r] : vr[tc][rt][r];
+                    vi[tc][rt][r] = k > l[tc] ? ci[tc][rt][r] : vi[tc][rt][r];
                 }
     };
-    // at slice k: the diagonal block's column for columns of slice k, zero for columns whose
-    // slice is beyond k in the sweep direction (`before`)
-    auto fix = [&](int k, bool down) {
+    // entry (row, column) and, below the diagonal block, its transpose: four consecutive rows
+    // per lane, so that the four lane groups fill a 128-byte line of the transposed row
+    auto store = [&](int k) {
 #pragma unroll
-        for (int tc = 0; tc < TC; ++tc) {
-            const bool here = k == l[tc];
-            const bool before = down ? k < l[tc] : k > l[tc];
+        for (int tc = 0; tc < TC; ++tc)
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
+            for (int rt = 0; rt < RT; ++rt) {
+                double xr[4], xi[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int y = 16 * rt + tile_row<T>(r, g);
-                    double2 d = cmk(0.0, 0.0);
-                    if (here) d = Gde[(size_t)k * W * W + y * W + y0[tc]];
-                    vr[tc][rt][r] = here ? (T)d.x : (before ? (T)0 : vr[tc][rt][r]);
-                    vi[tc][rt][r] = here ? (T)d.y : (before ? (T)0 : vi[tc][rt][r]);
+                    xr[r] = vr[tc][rt][r];
+                    xi[r] = vi[tc][rt][r];
+                    if (!STORE_G) xr[r] = xr[r] * xr[r] + xi[r] * xi[r];
+                    const size_t row = k * W + 16 * rt + tile_row<T>(r, g);
+                    if (valid[tc] && k >= l[tc]) {
+                        if (STORE_G) Ge[row * ldG + col[tc]] = cmk(xr[r], xi[r]);
+                        else Pe[row * ldP + col[tc]] = xr[r];
+                    }
                 }
-        }
+                if (sizeof(T) == 8) {
+                    transpose_groups(xr);
+                    if (STORE_G) transpose_groups(xi);
+                }
+                if (valid[tc] && k > l[tc]) {
+                    const size_t c4 = k * W + 16 * rt + 4 * g;
+                    if (STORE_G) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            Ge[(size_t)col[tc] * ldG + c4 + r] = cmk(xr[r], xi[r]);
+                    } else {
+                        *reinterpret_cast<double4*>(Pe + (size_t)col[tc] * ldP + c4) =
+                            double4{xr[0], xr[1], xr[2], xr[3]};
+                    }
+                }
+            }
     };
-    auto store = [&](int k, bool down) {
+    // Exit weights into L of the rows of slice k, from the columns of slice 0 in X: wavefront w
+    // takes YPW rows, the lanes of a row AC of the W terms Re conj(x_a) (Gamma x)_a each.
+    constexpr int YPW = W / NW, AC = W * YPW / 64;
+    auto exit_left = [&](int k) {
+        const double2* x = X[k & 1];
+        const int y = YPW * (tid >> 6) + lane % YPW, a0 = AC * (lane / YPW);
+        double acc = 0.0;
 #pragma unroll
-        for (int tc = 0; tc < TC; ++tc) {
-            const bool on = valid[tc] && (down ? k >= l[tc] : k < l[tc]);
-            if (!on) continue;
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int y = 16 * rt + tile_row<T>(r, g);
-                    const double xr = vr[tc][rt][r], xi = vi[tc][rt][r];
-                    if (STORE_G)
-                        Ge[(size_t)(k * W + y) * ldG + col[tc]] = cmk(xr, xi);
-                    else
-                        Pe[(size_t)(k * W + y) * ldP + col[tc]] = xr * xr + xi * xi;
-                }
+        for (int a = 0; a < AC; ++a) {
+            double2 u = cmk(0.0, 0.0);
+#pragma unroll 8
+            for (int b = 0; b < W; ++b) u = cadd(u, cscale(x[b * W + y], Gs[(a0 + a) * W + b]));
+            const double2 xa = x[(a0 + a) * W + y];
+            acc = fma(xa.x, u.x, fma(xa.y, u.y, acc));
         }
+#pragma unroll
+        for (int o = YPW; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
+        if (lane < YPW) wL[(size_t)e * N + k * W + y] = acc;
     };
     // Re v^+ Gamma v per column (Gamma real symmetric): u = Gamma v on the matrix cores, the
     // row sum of Re(conj(v) u) over the four lanes of each column; lane g = 0 gets the result.
@@ -392,66 +522,62 @@ __global__ void __launch_bounds__(64 * NW) fullinv_mfma_kernel(const double2* __
         return q;
     };
 
-    // ---- downward: k = kmin .. L-1 (gR) -------------------------------------------------
 #pragma unroll
     for (int tc = 0; tc < TC; ++tc)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) vr[tc][rt][r] = vi[tc][rt][r] = (T)0;
-    stage_block<W, 64 * NW>(Ms, gRe + (size_t)kmin * W * W, tid);
+            for (int r = 0; r < 4; ++r) {
+                const double2 d =
+                    Gde[((size_t)l[tc] * W + 16 * rt + tile_row<T>(r, g)) * W + y0[tc]];
+                vr[tc][rt][r] = (T)d.x;
+                vi[tc][rt][r] = (T)d.y;
+            }
+    if (slice0)
+        for (int i = tid; i < W * W; i += 64 * NW) Gs[i] = gme[i];
+    StagedBlock<W, 64 * NW> st;  // block k + 1 at the top of slice k
+    st.load(gRe + (size_t)kmin * W * W, tid);
+    st.write(Ms, tid);
+    st.load(gRe + (size_t)min(kmin + 1, L - 1) * W * W, tid);
     for (int k = kmin; k < L; ++k) {
         __syncthreads();
         const int b = (k - kmin) & 1;
-        if (k + 1 < L)
-            stage_block<W, 64 * NW>(Ms + (b ^ 1) * BS, gRe + (size_t)(k + 1) * W * W, tid);
-        product(Ms + b * BS);
-        fix(k, true);
-        store(k, true);
-    }
-    if (!STORE_G) {
+        st.write(Ms + (b ^ 1) * BS, tid);
+        st.load(gRe + (size_t)min(k + 2, L - 1) * W * W, tid);
+        if (slice0 && k > 0) exit_left(k - 1);
+        product(Ms + b * BS, k);
+        store(k);
+        if (slice0 && tid < 64) {
 #pragma unroll
-        for (int tc = 0; tc < TC; ++tc) {
-            const double q = quad(tc);
-            if (valid[tc] && g == 0) wR[(size_t)e * N + col[tc]] = q;
-            if (valid[tc] && l[tc] == 0) {
+            for (int tc = 0; tc < W / 16; ++tc)
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        cRL[(16 * rt + tile_row<T>(r, g)) * W + y0[tc]] = cmk(vr[tc][rt][r], vi[tc][rt][r]);
-            }
+                        X[k & 1][(16 * tc + n) * W + 16 * rt + tile_row<T>(r, g)] =
+                            cmk(vr[tc][rt][r], vi[tc][rt][r]);
         }
     }
-    // ---- upward: k = kmax .. 0 (gL) -----------------------------------------------------
-#pragma unroll
-    for (int tc = 0; tc < TC; ++tc)
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) vr[tc][rt][r] = vi[tc][rt][r] = (T)0;
-    __syncthreads();
-    stage_block<W, 64 * NW>(Ms, gLe + (size_t)kmax * W * W, tid);
-    for (int k = kmax; k >= 0; --k) {
+    if (STORE_G) return;
+    if (slice0) {  // the whole workgroup
         __syncthreads();
-        const int b = (kmax - k) & 1;
-        if (k > 0) stage_block<W, 64 * NW>(Ms + (b ^ 1) * BS, gLe + (size_t)(k - 1) * W * W, tid);
-        product(Ms + b * BS);
-        fix(k, false);
-        store(k, false);
+        exit_left(L - 1);
     }
-    if (!STORE_G) {
 #pragma unroll
-        for (int tc = 0; tc < TC; ++tc) {
-            const double q = quad(tc);
-            if (valid[tc] && g == 0) wL[(size_t)e * N + col[tc]] = q;
-            if (valid[tc] && l[tc] == L - 1) {
+    for (int tc = 0; tc < TC; ++tc) {
+        const double q = quad(tc);
+        if (valid[tc] && g == 0) wR[(size_t)e * N + col[tc]] = q;
+        if (valid[tc] && l[tc] == 0) {
+            double2* cRL = corner + (size_t)e * 2 * W * W;
+            double2* cLR = cRL + W * W;  // its transpose
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
+            for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        cLR[(16 * rt + tile_row<T>(r, g)) * W + y0[tc]] = cmk(vr[tc][rt][r], vi[tc][rt][r]);
-            }
+                for (int r = 0; r < 4; ++r) {
+                    const int y = 16 * rt + tile_row<T>(r, g);
+                    cRL[y * W + y0[tc]] = cmk(vr[tc][rt][r], vi[tc][rt][r]);
+                    cLR[y0[tc] * W + y] = cmk(vr[tc][rt][r], vi[tc][rt][r]);
+                }
         }
     }
 }
@@ -459,11 +585,10 @@ __global__ void __launch_bounds__(64 * NW) fullinv_mfma_kernel(const double2* __
 template <int W, int TC, int NW, bool STORE_G, typename T = double>
 static hipError_t launch_fullinv_mfma(const mcnegf_kernel& k, double2* Gc, int64_t ldG,
                                       hipStream_t s) {
-    dim3 grid((k.N + 16 * TC * NW - 1) / (16 * TC * NW), k.nE);
+    dim3 grid(k.nE, (k.N + 16 * TC * NW - 1) / (16 * TC * NW));
     {
         MCNEGF_TIMED(STORE_G ? "fullinv_store_g_kernel" : "fullinv_kernel", s);
         hipLaunchKernelGGL((fullinv_mfma_kernel<W, TC, NW, STORE_G, T>), grid, dim3(64 * NW), 0, s,
-                           reinterpret_cast<const double2*>(k.gL),
                            reinterpret_cast<const double2*>(k.gR),
                            reinterpret_cast<const double2*>(k.Gd), k.gam_lead, k.L, k.t, k.p_pitch,
                            k.P, k.wL, k.wR, reinterpret_cast<double2*>(k.corner), Gc, ldG);
@@ -487,10 +612,10 @@ static hipError_t launch_fullinv_any(const mcnegf_kernel& k, double2* Gc, int64_
         MCNEGF_CASE(1) MCNEGF_CASE(2) MCNEGF_CASE(3) MCNEGF_CASE(4) MCNEGF_CASE(5)
         MCNEGF_CASE(6) MCNEGF_CASE(7) MCNEGF_CASE(8) MCNEGF_CASE(9) MCNEGF_CASE(10)
         MCNEGF_CASE(11) MCNEGF_CASE(12) MCNEGF_CASE(13) MCNEGF_CASE(14) MCNEGF_CASE(15)
-        MCNEGF_CASE(16) MCNEGF_CASE(17) MCNEGF_CASE(18) MCNEGF_CASE(19) MCNEGF_CASE(20)
+        MCNEGF_CASE(17) MCNEGF_CASE(18) MCNEGF_CASE(19) MCNEGF_CASE(20)
         MCNEGF_CASE(21) MCNEGF_CASE(22) MCNEGF_CASE(23) MCNEGF_CASE(24) MCNEGF_CASE(25)
         MCNEGF_CASE(26) MCNEGF_CASE(27) MCNEGF_CASE(28) MCNEGF_CASE(29) MCNEGF_CASE(30)
-        MCNEGF_CASE(31) MCNEGF_CASE(32)
+        MCNEGF_CASE(31)
 #undef MCNEGF_CASE
         default:
             return hipErrorInvalidValue;
