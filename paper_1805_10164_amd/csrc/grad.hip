@@ -21,10 +21,15 @@
 //   lead parts:  sum_j G_ij u_j conj(G_{j,sp+b}) = conj(R_{i,sp+b}),
 //                sum_j G_ij v_j conj(G_{j,sq+b}) = conj(Q_{i,sq+b}).
 // A column of Q or R is conj(A)^{-1} applied to d o G_{:,c} (A = E - H - Sigma, block
-// tridiagonal with off-diagonal blocks t I), solved by the block LU of A that the stored
-// left-connected blocks gL_k provide:
-//   forward   y_k = conj(gL_k) (h_k - t y_{k-1}),   backward  q_k = y_k - t conj(gL_k) q_{k+1},
-// O(N W) per column instead of a dense O(N^2) product.
+// tridiagonal with off-diagonal blocks t I), by the block LDL^T of A that the stored
+// left-connected blocks gL_k provide (A is complex symmetric: D_k = gL_k^{-1}):
+//   forward   w_k = h_k - t y_{k-1},  y_k = conj(gL_k) w_k,
+//   backward  q_k = y_k - t conj(gL_k) q_{k+1}.
+// The dense part is a quadratic form of column c alone, with h^u = u o G_{:,c}, h^v = v o G_{:,c}
+//   sum_a G_ac u_a Q_ac = (h^u)^T conj(A)^{-1} h^v = sum_k (w^u_k)^T y^v_k,
+// so two forward eliminations in one pass over G give it, O(N W) per column and nothing stored;
+// only the 2 W lead columns take the backward sweep.  (A full solve per column read G twice and
+// wrote and read its forward result: four times the traffic.)
 #include "common.h"
 
 namespace mcnegf {
@@ -151,112 +156,376 @@ __device__ inline void conj_block_matvec(double2 (&out)[W], const double2 (&in)[
     }
 }
 
-// One thread per right-hand side c of one energy: c < N is column c of Q (d = v), c = N + b
-// is column sp + b of R (d = u).  The forward sweep keeps y in Y[.][c]; the backward sweep
-// overwrites it with q only where the assembly reads it (columns sq.. sq+W-1 and N..N+W-1),
-// and for c < N accumulates, over the rows a of the column,
-//   kd = sum_a G_ac u_a Q_ac,  kg = sum_a G_ac^2 u_a x_a,  pv = sum_a |G_ac|^2 v_a,  pu (u).
-template <int W>
-__global__ void __launch_bounds__(64) adjoint_solve_kernel(
-    const double2* __restrict__ gL, const double2* __restrict__ Gc, const double* __restrict__ xl,
-    const double* __restrict__ gamma, int L, double t, int64_t ld, int64_t ldY,
-    uint32_t inject_lead, double2* __restrict__ Y, double2* __restrict__ part_k,
-    double* __restrict__ part_p) {
-    const int N = W * L;
-    const int NC = N + W;
-    const int e = blockIdx.y;
-    // One wavefront per workgroup; the blocks gL_k are staged in LDS one slice ahead
-    // (double-buffered, one barrier per slice); idle lanes compute on column 0.
-    __shared__ double Ms_raw[2 * 2 * W * W];  // two buffers of W x W (re, im)
-    const int tid = threadIdx.x;
-    const int c = blockIdx.x * 64 + tid;
-    const bool valid = c < NC;
-    const bool dense = c < N;
-    const int sp = inject_lead == 0 ? 0 : (L - 1) * W;
-    const int sq = inject_lead == 0 ? (L - 1) * W : 0;
-    const int col = dense ? c : (valid ? sp + (c - N) : 0);
-    const bool keep_q = valid && (!dense || (c >= sq && c < sq + W));
-    const int cl = valid ? c : 0;  // column that idle lanes read
-    const double2* Ge = Gc + (size_t)e * N * ld;
-    double2* Ye = Y + (size_t)e * N * ldY;
-    const double* xe = xl + (size_t)e * 2 * ld;
-    const double* le = xe + ld;
-    const double2* gLe = gL + (size_t)e * L * W * W;
-    lds_double* Ms = (lds_double*)Ms_raw;
-    constexpr int BS = 2 * W * W;  // doubles per buffer
-    // the 64 lanes copy block gL_slice into LDS buffer buf
-    auto stage = [&](int buf, int slice) {
+// The W x W block src into the LDS buffer dst by NT threads.
+template <int W, int NT>
+__device__ inline void stage_block(lds_double* dst, const double2* __restrict__ src, int tid) {
 #pragma unroll
-        for (int i = tid; i < W * W; i += 64) {
-            const double2 v = gLe[(size_t)slice * W * W + i];
-            Ms[buf * BS + 2 * i] = v.x;
-            Ms[buf * BS + 2 * i + 1] = v.y;
-        }
-    };
+    for (int i = tid; i < W * W; i += NT) {
+        const double2 v = src[i];
+        dst[2 * i] = v.x;
+        dst[2 * i + 1] = v.y;
+    }
+}
 
+struct AdjointArgs {
+    const double2* gL;     // [nE][L][W][W]
+    const double2* G;      // [nE][N][ld]
+    const double* xl;      // [nE][2][ld] x, lambda
+    const double* gamma;   // [N]
+    double2* Y;            // [nE][N][ldY]: columns sq .. of Q and N .. of R
+    double2* part_k;       // [nE][2][N]
+    double* part_p;        // [nE][2][N]
+    int L;
+    double t;
+    int64_t ld, ldY;
+    uint32_t inject_lead;
+};
+
+// The lead columns of one energy, on one wavefront: right-hand side c < W is
+// column sq + c of Q (d = v), c = W + b is column sp + b of R (d = u), one lane each; y goes to Y and q replaces it.  A chain of 2 L slices: it shares its launch
+// with the dense columns.
+template <int W>
+__device__ inline void adjoint_lead_columns(const AdjointArgs& a, int e, lds_double* Ms) {
+    constexpr int BS = 2 * W * W;
+    const int N = W * a.L;
+    const int tid = threadIdx.x;
+    const bool on = tid < 2 * W;
+    const int sp = a.inject_lead == 0 ? 0 : N - W;
+    const int sq = a.inject_lead == 0 ? N - W : 0;
+    const bool isq = tid < W;
+    const int col = isq ? sq + tid : sp + tid - W;  // column of G
+    const int yc = isq ? sq + tid : N + tid - W;    // column of Y
+    const double2* Ge = a.G + (size_t)e * N * a.ld;
+    double2* Ye = a.Y + (size_t)e * N * a.ldY;
+    const double* xe = a.xl + (size_t)e * 2 * a.ld;
+    const double* de = isq ? xe : xe + a.ld;
+    const double2* gLe = a.gL + (size_t)e * a.L * W * W;
     double2 y[W], z[W];
 #pragma unroll
     for (int r = 0; r < W; ++r) y[r] = cmk(0.0, 0.0);
-    stage(0, 0);
-    for (int k = 0; k < L; ++k) {
-        __syncthreads();  // block k visible in buffer k & 1; buffer (k + 1) & 1 no longer read
-        const lds_double* cur = Ms + (k & 1) * BS;
-        if (k + 1 < L) stage((k + 1) & 1, k + 1);
-#pragma unroll
-        for (int r = 0; r < W; ++r) {
-            const int row = k * W + r;
-            const double d = gamma[row] * (dense ? xe[row] : le[row]);
-            const double2 g = Ge[(size_t)row * ld + col];
-            z[r] = cmk(fma(d, g.x, -t * y[r].x), fma(d, g.y, -t * y[r].y));
-        }
-        conj_block_matvec<W>(y, z, cur);
-        if (valid) {
-#pragma unroll
-            for (int r = 0; r < W; ++r) Ye[(size_t)(k * W + r) * ldY + c] = y[r];
-        }
-    }
-    // y now holds y_{L-1} = q_{L-1}; the backward sweep stages gL_{L-2}, gL_{L-3}, ...
-    double2 kd = cmk(0.0, 0.0), kg = cmk(0.0, 0.0);
-    double pv = 0.0, pu = 0.0;
-    __syncthreads();  // forward reads of both buffers done
-    if (L > 1) stage(0, L - 2);
-    for (int k = L - 1; k >= 0; --k) {
-        if (k < L - 1) {
-            const int j = L - 2 - k;  // 0, 1, ... : buffer parity
-            __syncthreads();
-            const lds_double* cur = Ms + (j & 1) * BS;
-            if (k > 0) stage((j + 1) & 1, k - 1);
-            conj_block_matvec<W>(z, y, cur);
-#pragma unroll
-            for (int r = 0; r < W; ++r) {
-                const double2 yk = Ye[(size_t)(k * W + r) * ldY + cl];
-                y[r] = cmk(fma(-t, z[r].x, yk.x), fma(-t, z[r].y, yk.y));
-            }
-        }
-        if (keep_q) {
-#pragma unroll
-            for (int r = 0; r < W; ++r) Ye[(size_t)(k * W + r) * ldY + c] = y[r];
-        }
-        if (dense) {
+    stage_block<W, 64>(Ms, gLe, tid);
+    for (int k = 0; k < a.L; ++k) {
+        __syncthreads();  // block k visible in buffer k & 1; the other is no longer read
+        if (k + 1 < a.L)
+            stage_block<W, 64>(Ms + ((k + 1) & 1) * BS, gLe + (size_t)(k + 1) * W * W, tid);
+        if (on) {
 #pragma unroll
             for (int r = 0; r < W; ++r) {
                 const int row = k * W + r;
-                const double2 g = Ge[(size_t)row * ld + col];
-                const double gm = gamma[row];
-                const double ua = gm * le[row], va = gm * xe[row];
-                cfma(kd, cscale(g, ua), y[r]);
-                kg = cadd(kg, cscale(cmul(g, g), ua * xe[row]));
-                const double p = cabs2(g);
-                pv = fma(p, va, pv);
-                pu = fma(p, ua, pu);
+                const double d = a.gamma[row] * de[row];
+                const double2 g = Ge[(size_t)row * a.ld + col];
+                z[r] = cmk(fma(d, g.x, -a.t * y[r].x), fma(d, g.y, -a.t * y[r].y));
+            }
+            conj_block_matvec<W>(y, z, Ms + (k & 1) * BS);
+#pragma unroll
+            for (int r = 0; r < W; ++r) Ye[(size_t)(k * W + r) * a.ldY + yc] = y[r];
+        }
+    }
+    // y now holds y_{L-1} = q_{L-1}; the backward sweep stages gL_{L-2}, gL_{L-3}, ...
+    __syncthreads();
+    if (a.L > 1) stage_block<W, 64>(Ms, gLe + (size_t)(a.L - 2) * W * W, tid);
+    for (int k = a.L - 2; k >= 0; --k) {
+        const int j = a.L - 2 - k;  // 0, 1, ... : buffer parity
+        __syncthreads();
+        if (k > 0)
+            stage_block<W, 64>(Ms + ((j + 1) & 1) * BS, gLe + (size_t)(k - 1) * W * W, tid);
+        if (on) {
+            conj_block_matvec<W>(z, y, Ms + (j & 1) * BS);
+#pragma unroll
+            for (int r = 0; r < W; ++r) {
+                double2* at = Ye + (size_t)(k * W + r) * a.ldY + yc;
+                y[r] = cmk(fma(-a.t, z[r].x, at->x), fma(-a.t, z[r].y, at->y));
+                *at = y[r];
             }
         }
     }
-    if (dense) {
-        part_k[((size_t)e * 2 + 0) * N + c] = kd;
-        part_k[((size_t)e * 2 + 1) * N + c] = kg;
-        part_p[((size_t)e * 2 + 0) * N + c] = pv;
-        part_p[((size_t)e * 2 + 1) * N + c] = pu;
+}
+
+__device__ inline double other_half(double v) {  // of lane + 32, in lanes 0 .. 31
+    auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(hi[1], lo[1]);
+}
+
+// Dense columns on the VALU: a wavefront owns 32 columns, lanes 0 .. 31 eliminate h^v, lanes
+// 32 .. 63 h^u, and the blocks gL_k are broadcast from LDS to both (double-buffered, one slice
+// ahead).  Per column
+//   kd = sum_k (w^u_k)^T y^v_k,  kg = sum_a G_ac^2 u_a x_a,  pv = sum_a |G_ac|^2 v_a,  pu (u).
+// The first workgroup of an energy takes the lead columns instead.
+template <int W>
+__global__ void __launch_bounds__(64) adjoint_solve_kernel(AdjointArgs a) {
+    constexpr int BS = 2 * W * W;  // doubles per buffer
+    __shared__ double Ms_raw[2 * BS];
+    lds_double* Ms = (lds_double*)Ms_raw;
+    const int e = blockIdx.y;
+    if (blockIdx.x == 0) {
+        adjoint_lead_columns<W>(a, e, Ms);
+        return;
+    }
+    const int N = W * a.L;
+    const int lane = threadIdx.x;
+    const bool half_u = lane >= 32;
+    const int c = (blockIdx.x - 1) * 32 + (lane & 31);
+    const int col = min(c, N - 1);
+    const double2* Ge = a.G + (size_t)e * N * a.ld;
+    const double* xe = a.xl + (size_t)e * 2 * a.ld;
+    const double* le = xe + a.ld;
+    const double2* gLe = a.gL + (size_t)e * a.L * W * W;
+    double2 y[W], w[W];
+#pragma unroll
+    for (int r = 0; r < W; ++r) y[r] = cmk(0.0, 0.0);
+    double2 kd = cmk(0.0, 0.0), kg = cmk(0.0, 0.0);
+    double pv = 0.0, pu = 0.0;
+    stage_block<W, 64>(Ms, gLe, lane);
+    for (int k = 0; k < a.L; ++k) {
+        __syncthreads();
+        if (k + 1 < a.L)
+            stage_block<W, 64>(Ms + ((k + 1) & 1) * BS, gLe + (size_t)(k + 1) * W * W, lane);
+#pragma unroll
+        for (int r = 0; r < W; ++r) {
+            const int row = k * W + r;
+            const double gm = a.gamma[row], x = xe[row];
+            const double ua = gm * le[row], va = gm * x;
+            const double d = half_u ? ua : va;
+            const double2 g = Ge[(size_t)row * a.ld + col];
+            w[r] = cmk(fma(d, g.x, -a.t * y[r].x), fma(d, g.y, -a.t * y[r].y));
+            kg = cadd(kg, cscale(cmul(g, g), ua * x));
+            const double p = cabs2(g);
+            pv = fma(p, va, pv);
+            pu = fma(p, ua, pu);
+        }
+        conj_block_matvec<W>(y, w, Ms + (k & 1) * BS);
+#pragma unroll
+        for (int r = 0; r < W; ++r)
+            cfma(kd, cmk(other_half(w[r].x), other_half(w[r].y)), y[r]);
+    }
+    if (!half_u && c < N) {
+        a.part_k[((size_t)e * 2 + 0) * N + c] = kd;
+        a.part_k[((size_t)e * 2 + 1) * N + c] = kg;
+        a.part_p[((size_t)e * 2 + 0) * N + c] = pv;
+        a.part_p[((size_t)e * 2 + 1) * N + c] = pu;
+    }
+}
+
+// Dense columns at W = 16 and 32 on the FP64 matrix cores: a wavefront owns TC tiles of 16
+// columns and both eliminations of each; lane (n, g) holds the rows 16 rt + 4 r + g of column n,
+// which is the accumulator layout of one product and the B operand of the next, so w and y
+// never leave registers; the staged block is the A operand (NW wavefronts share it).  G is read
+// one slice ahead, under the products (64 clocks each, 4 (W / 4) (W / 16) per complex tile).
+// N = 3200, 128 energies: 22.9 -> 7.6 ms (44 TFLOP/s; G read at 2.8 TB/s); W = 32, N = 4160,
+// 16 energies 25.5 -> 4.1 ms.
+typedef double dmfma4 __attribute__((ext_vector_type(4)));
+
+// (yr, yi)[i] = conj(M) (wr, wi)[i] for V vectors, M staged in LDS.
+template <int W, int V>
+__device__ inline void conj_product(dmfma4 (&yr)[V][W / 16], dmfma4 (&yi)[V][W / 16],
+                                    const dmfma4 (&wr)[V][W / 16], const dmfma4 (&wi)[V][W / 16],
+                                    const lds_double* M, int n, int g) {
+#pragma unroll
+    for (int rt = 0; rt < W / 16; ++rt) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) yr[i][rt] = yi[i][rt] = dmfma4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < W / 4; ++s) {
+            const int at = 2 * ((16 * rt + n) * W + 4 * s + g);
+            const double ar = M[at], ai = M[at + 1];  // conj: ar - i ai
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                const double br = wr[i][s >> 2][s & 3], bi = wi[i][s >> 2][s & 3];
+                yr[i][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, yr[i][rt], 0, 0, 0);
+                yi[i][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, yi[i][rt], 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < V; ++i) {
+                const double br = wr[i][s >> 2][s & 3], bi = wi[i][s >> 2][s & 3];
+                yr[i][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, bi, yr[i][rt], 0, 0, 0);
+                yi[i][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, br, yi[i][rt], 0, 0, 0);
+            }
+        }
+    }
+}
+
+// The lead columns of one energy (see adjoint_lead_columns), 16 per wavefront.
+template <int W>
+__device__ inline void adjoint_lead_mfma(const AdjointArgs& a, int e, lds_double* Ms) {
+    constexpr int RT = W / 16, BS = 2 * W * W, NT = 8 * W;  // 2 W columns: W / 8 wavefronts
+    const int N = W * a.L;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int n = lane & 15, g = lane >> 4;
+    const int sp = a.inject_lead == 0 ? 0 : N - W;
+    const int sq = a.inject_lead == 0 ? N - W : 0;
+    const int c = 16 * (tid >> 6) + n;
+    const bool isq = c < W;
+    const int col = isq ? sq + c : sp + c - W;  // column of G
+    const int yc = isq ? sq + c : N + c - W;    // column of Y
+    const double2* Ge = a.G + (size_t)e * N * a.ld;
+    double2* Ye = a.Y + (size_t)e * N * a.ldY;
+    const double* xe = a.xl + (size_t)e * 2 * a.ld;
+    const double* de = isq ? xe : xe + a.ld;
+    const double2* gLe = a.gL + (size_t)e * a.L * W * W;
+    dmfma4 yr[1][RT], yi[1][RT], wr[1][RT], wi[1][RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) yr[0][rt] = yi[0][rt] = dmfma4{0, 0, 0, 0};
+    stage_block<W, NT>(Ms, gLe, tid);
+    for (int k = 0; k < a.L; ++k) {
+        __syncthreads();
+        if (k + 1 < a.L)
+            stage_block<W, NT>(Ms + ((k + 1) & 1) * BS, gLe + (size_t)(k + 1) * W * W, tid);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = k * W + 16 * rt + 4 * r + g;
+                const double d = a.gamma[row] * de[row];
+                const double2 v = Ge[(size_t)row * a.ld + col];
+                wr[0][rt][r] = fma(d, v.x, -a.t * yr[0][rt][r]);
+                wi[0][rt][r] = fma(d, v.y, -a.t * yi[0][rt][r]);
+            }
+        conj_product<W, 1>(yr, yi, wr, wi, Ms + (k & 1) * BS, n, g);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                Ye[(size_t)(k * W + 16 * rt + 4 * r + g) * a.ldY + yc] =
+                    cmk(yr[0][rt][r], yi[0][rt][r]);
+    }
+    __syncthreads();
+    if (a.L > 1) stage_block<W, NT>(Ms, gLe + (size_t)(a.L - 2) * W * W, tid);
+    for (int k = a.L - 2; k >= 0; --k) {
+        const int j = a.L - 2 - k;
+        __syncthreads();
+        if (k > 0)
+            stage_block<W, NT>(Ms + ((j + 1) & 1) * BS, gLe + (size_t)(k - 1) * W * W, tid);
+        conj_product<W, 1>(wr, wi, yr, yi, Ms + (j & 1) * BS, n, g);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                double2* at = Ye + (size_t)(k * W + 16 * rt + 4 * r + g) * a.ldY + yc;
+                yr[0][rt][r] = fma(-a.t, wr[0][rt][r], at->x);
+                yi[0][rt][r] = fma(-a.t, wi[0][rt][r], at->y);
+                *at = cmk(yr[0][rt][r], yi[0][rt][r]);
+            }
+    }
+}
+
+// One workgroup of W / 8 wavefronts: the lead columns (first workgroup of an energy), else
+// 16 TC dense columns per wavefront, TC = 32 / W.
+template <int W>
+__global__ void __launch_bounds__(8 * W, 2) adjoint_mfma_kernel(AdjointArgs a) {
+    constexpr int TC = 32 / W, NW = W / 8;
+    constexpr int RT = W / 16, BS = 2 * W * W, NT = 64 * NW;
+    __shared__ double Ms_raw[2 * BS];
+    lds_double* Ms = (lds_double*)Ms_raw;
+    const int e = blockIdx.y;
+    if (blockIdx.x == 0) {
+        adjoint_lead_mfma<W>(a, e, Ms);
+        return;
+    }
+    const int N = W * a.L;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int n = lane & 15, g = lane >> 4;
+    const int c0 = ((blockIdx.x - 1) * NW + (tid >> 6)) * 16 * TC;
+    const double2* Ge = a.G + (size_t)e * N * a.ld;
+    const double* xe = a.xl + (size_t)e * 2 * a.ld;
+    const double* le = xe + a.ld;
+    const double2* gLe = a.gL + (size_t)e * a.L * W * W;
+    int col[TC];
+    double2 kd[TC], kg[TC];
+    double pv[TC], pu[TC];
+#pragma unroll
+    for (int tc = 0; tc < TC; ++tc) {
+        col[tc] = min(c0 + 16 * tc + n, N - 1);
+        kd[tc] = kg[tc] = cmk(0.0, 0.0);
+        pv[tc] = pu[tc] = 0.0;
+    }
+    // [2 tile + (0: u, 1: v)][row tile]: y of the previous slice, then w of this one
+    dmfma4 wr[2 * TC][RT], wi[2 * TC][RT];
+#pragma unroll
+    for (int i = 0; i < 2 * TC; ++i)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) wr[i][rt] = wi[i][rt] = dmfma4{0, 0, 0, 0};
+    dmfma4 gr[TC][RT], gi[TC][RT], gam[RT], xk[RT], lk[RT];
+    auto read = [&](int k) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = k * W + 16 * rt + 4 * r + g;
+                gam[rt][r] = a.gamma[row];
+                xk[rt][r] = xe[row];
+                lk[rt][r] = le[row];
+#pragma unroll
+                for (int tc = 0; tc < TC; ++tc) {
+                    const double2 v = Ge[(size_t)row * a.ld + col[tc]];
+                    gr[tc][rt][r] = v.x;
+                    gi[tc][rt][r] = v.y;
+                }
+            }
+    };
+    read(0);
+    stage_block<W, NT>(Ms, gLe, tid);
+    for (int k = 0; k < a.L; ++k) {
+        __syncthreads();
+        if (k + 1 < a.L)
+            stage_block<W, NT>(Ms + ((k + 1) & 1) * BS, gLe + (size_t)(k + 1) * W * W, tid);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double ua = gam[rt][r] * lk[rt][r], va = gam[rt][r] * xk[rt][r];
+                const double ux = ua * xk[rt][r];
+#pragma unroll
+                for (int tc = 0; tc < TC; ++tc) {
+                    const double2 v = cmk(gr[tc][rt][r], gi[tc][rt][r]);
+                    wr[2 * tc][rt][r] = fma(ua, v.x, -a.t * wr[2 * tc][rt][r]);
+                    wi[2 * tc][rt][r] = fma(ua, v.y, -a.t * wi[2 * tc][rt][r]);
+                    wr[2 * tc + 1][rt][r] = fma(va, v.x, -a.t * wr[2 * tc + 1][rt][r]);
+                    wi[2 * tc + 1][rt][r] = fma(va, v.y, -a.t * wi[2 * tc + 1][rt][r]);
+                    kg[tc] = cadd(kg[tc], cscale(cmul(v, v), ux));
+                    const double p = cabs2(v);
+                    pv[tc] = fma(p, va, pv[tc]);
+                    pu[tc] = fma(p, ua, pu[tc]);
+                }
+            }
+        read(min(k + 1, a.L - 1));
+        __builtin_amdgcn_sched_barrier(0);  // the loads go ahead of the products
+        dmfma4 yr[2 * TC][RT], yi[2 * TC][RT];
+        conj_product<W, 2 * TC>(yr, yi, wr, wi, Ms + (k & 1) * BS, n, g);
+#pragma unroll
+        for (int tc = 0; tc < TC; ++tc)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    cfma(kd[tc], cmk(wr[2 * tc][rt][r], wi[2 * tc][rt][r]),
+                         cmk(yr[2 * tc + 1][rt][r], yi[2 * tc + 1][rt][r]));
+#pragma unroll
+        for (int i = 0; i < 2 * TC; ++i)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                wr[i][rt] = yr[i][rt];
+                wi[i][rt] = yi[i][rt];
+            }
+    }
+    auto over_groups = [](double v) {  // the four lanes of a column
+        v += __shfl_xor(v, 16, 64);
+        return v + __shfl_xor(v, 32, 64);
+    };
+#pragma unroll
+    for (int tc = 0; tc < TC; ++tc) {
+        const double2 d = cmk(over_groups(kd[tc].x), over_groups(kd[tc].y));
+        const double2 q = cmk(over_groups(kg[tc].x), over_groups(kg[tc].y));
+        const double sv = over_groups(pv[tc]), su = over_groups(pu[tc]);
+        const int c = c0 + 16 * tc + n;
+        if (g == 0 && c < N) {
+            a.part_k[((size_t)e * 2 + 0) * N + c] = d;
+            a.part_k[((size_t)e * 2 + 1) * N + c] = q;
+            a.part_p[((size_t)e * 2 + 0) * N + c] = sv;
+            a.part_p[((size_t)e * 2 + 1) * N + c] = su;
+        }
     }
 }
 
@@ -364,11 +633,19 @@ __global__ void grad_reduce_kernel(const double* __restrict__ gV, const double* 
 template <int W>
 static hipError_t launch_adjoint_w(const mcnegf_kernel& k, const GradBuffers& gb,
                                    uint32_t inject_lead, hipStream_t s) {
+    const AdjointArgs a = {reinterpret_cast<const double2*>(k.gL), gb.G, gb.xl, k.gamma, gb.Y,
+                           gb.part_k, gb.part_p, k.L, k.t, gb.ld, gb.ldY, inject_lead};
     {
+        // one workgroup of lead columns, then the dense ones
         MCNEGF_TIMED("adjoint_solve_kernel", s);
-        hipLaunchKernelGGL(adjoint_solve_kernel<W>, dim3((k.N + W + 63) / 64, k.nE), dim3(64),
-                           0, s, reinterpret_cast<const double2*>(k.gL), gb.G, gb.xl, k.gamma, k.L,
-                           k.t, gb.ld, gb.ldY, inject_lead, gb.Y, gb.part_k, gb.part_p);
+        if constexpr (W == 16 || W == 32) {
+            // 64 columns per workgroup: W / 8 wavefronts of 32 / W tiles of 16
+            hipLaunchKernelGGL(adjoint_mfma_kernel<W>, dim3(1 + (k.N + 63) / 64, k.nE),
+                               dim3(8 * W), 0, s, a);
+        } else {
+            hipLaunchKernelGGL(adjoint_solve_kernel<W>, dim3(1 + (k.N + 31) / 32, k.nE), dim3(64),
+                               0, s, a);
+        }
     }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
