@@ -236,8 +236,16 @@ __device__ inline double kernel_weight(const AliasArgs& a, int e, int row, int i
 // b_i K_row,i), written to the caller's tables; rho = modified total / unmodified total is
 // stored per row, the injection rows' unmodified totals c_p as the plain build stores them,
 // and the row-total checks of the build are left alone.
-template <int BT, int KM, bool kBias = false>
-__global__ void __launch_bounds__(BT) alias_build_kernel(AliasArgs a) {
+// KM is the row's own count of items per thread, so that only the last KP items of a thread can
+// lie beyond the row (every check that is not needed costs instructions, which bound this
+// kernel); the order of the items, and with it the table, depends on BT alone.
+// Wavefronts per SIMD the registers are held to: all eight with 128 threads per row (1.04 ->
+// 1.02 ms at W = 10, N = 1000, 256 energies); 512 threads spill sooner (6.1 -> 6.4 ms over six
+// W = 8 wires when held to 6 or 8).
+constexpr int alias_waves(int BT) { return BT == 128 ? 8 : 1; }
+
+template <int BT, int KM, int KP, bool kBias = false>
+__global__ void __launch_bounds__(BT, alias_waves(BT)) alias_build_kernel(AliasArgs a) {
     constexpr bool kLong = KM > 8;  // rows above BT * 8 outcomes
     extern __shared__ double smem[];
     __shared__ double sd[BT / 64];  // one partial per wavefront
@@ -255,6 +263,8 @@ __global__ void __launch_bounds__(BT) alias_build_kernel(AliasArgs a) {
     auto heavyC = [&](int m) -> double& { return lh[n - m]; };
     auto heavyIdx = [&](int m) -> uint16_t& { return kLong ? idx[n - 1 - m] : idx[m]; };
 
+    // item k of this thread lies in the row
+    auto in_row = [&](int k, int i) { return k + KP < KM || i < n; };
     const double* lead = a.lead + (size_t)e * MCNEGF_LEAD_NTERMS;
     // 1. weights of this row (items beyond n weigh 0 and are skipped below)
     double w[KM];
@@ -263,9 +273,9 @@ __global__ void __launch_bounds__(BT) alias_build_kernel(AliasArgs a) {
 #pragma unroll
     for (int k = 0; k < KM; ++k) {
         const int i = tid + BT * k;
-        double v = i < n ? kernel_weight(a, e, row, i) : 0.0;
+        double v = in_row(k, i) ? kernel_weight(a, e, row, i) : 0.0;
         if constexpr (kBias) {
-            const double b = i < n ? a.bias[(size_t)e * n + i] : 0.0;
+            const double b = in_row(k, i) ? a.bias[(size_t)e * n + i] : 0.0;
             bad_bias |= !(b >= 0.0 && b <= 1.7976931348623157e308);
             part0 += v;
             v *= b;
@@ -326,7 +336,7 @@ __global__ void __launch_bounds__(BT) alias_build_kernel(AliasArgs a) {
     for (int k = 0; k < KM; ++k) {
         const double v = w[k] * scale;
         w[k] = v;
-        if ((tid + BT * k) < n) {
+        if (in_row(k, tid + BT * k)) {
             if (v < 1.0) { dl += 1.0 - v; ++nl; }
             else { uh += v - 1.0; ++nh; }
         }
@@ -336,19 +346,16 @@ __global__ void __launch_bounds__(BT) alias_build_kernel(AliasArgs a) {
     block_scan2<BT>(dl, nl, Dtot, NLtot, sd, si);
     block_scan2<BT>(uh, nh, Utot, NHtot, sd, si);
     int rk[KM];     // light rank, or ~heavy rank
-    double dc[KM];  // light start D, or heavy end C
 #pragma unroll
     for (int k = 0; k < KM; ++k) {
         const int i = tid + BT * k;
         const double v = w[k];
         rk[k] = 0;
-        dc[k] = 0.0;
-        if (i < n) {
+        if (in_row(k, i)) {
             if (v < 1.0) {
                 lightD(nl) = dl;
                 if (kLong) idx[nl] = (uint16_t)i;
                 rk[k] = nl;
-                dc[k] = dl;
                 dl += 1.0 - v;
                 ++nl;
             } else {
@@ -356,7 +363,6 @@ __global__ void __launch_bounds__(BT) alias_build_kernel(AliasArgs a) {
                 heavyC(nh) = uh;
                 heavyIdx(nh) = (uint16_t)i;
                 rk[k] = ~nh;
-                dc[k] = uh;
                 ++nh;
             }
         }
@@ -438,7 +444,7 @@ __global__ void __launch_bounds__(BT) alias_build_kernel(AliasArgs a) {
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
             const int i = tid + BT * k;
-            if (i >= n) continue;
+            if (!in_row(k, i)) continue;
             const int r = rk[k];
             uint32_t packed, low;
             if (NHtot == 0) {
@@ -478,7 +484,7 @@ __global__ void __launch_bounds__(BT) alias_build_kernel(AliasArgs a) {
 #pragma unroll
             for (int k = 0; k < KM; ++k) {
                 const int i = tid + BT * k;
-                if (i < n) {
+                if (in_row(k, i)) {
                     out[i] = (0xFFFFFFFFu & ~kAliasIdxMask) | (uint32_t)i;
                     out_lo[i] = (uint16_t)(0xFFFFFFFFu & kAliasIdxMask);
                 }
@@ -556,7 +562,7 @@ __global__ void __launch_bounds__(BT) alias_build_kernel(AliasArgs a) {
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
             const int i = tid + BT * k;
-            if (i < n) {
+            if (in_row(k, i)) {
                 const uint64_t v = slots[i];
                 out[i] = (uint32_t)v;
                 out_lo[i] = (uint16_t)(v >> 32);
@@ -650,15 +656,36 @@ static hipError_t launch_alias_rows(const mcnegf_kernel& k, const AliasArgs& a,
                                     const char* name, hipStream_t s) {
     const int n = k.n_out;
     const size_t lds = (size_t)(n + 1) * 8 + (size_t)n * 2;
-    // rows up to 1024 outcomes: 128 threads x 8 items; up to 1536: 256 x 6; up to 4096:
-    // 512 x 8; up to 8192: 512 x 16; longer rows (n <= kMaxOut): 512 x 32
-    const int shape = n <= 128 * 8 ? 0 : n <= 256 * 6 ? 1 : n <= 512 * 8 ? 2 : n <= 512 * 16 ? 3 : 4;
-    const void* fns[5] = {(const void*)alias_build_kernel<128, 8, kBias>,
-                          (const void*)alias_build_kernel<256, 6, kBias>,
-                          (const void*)alias_build_kernel<512, 8, kBias>,
-                          (const void*)alias_build_kernel<512, 16, kBias>,
-                          (const void*)alias_build_kernel<512, 32, kBias>};
-    const int bts[5] = {128, 256, 512, 512, 512};
+    // Threads per row (they fix the order of the items): 128 up to 1024 outcomes, 256 up to
+    // 1536, 512 above; items per thread as the row needs, above 8 by steps of 2 (up to 16) and
+    // of 4 (at most 32: n <= kMaxOut).  Against 128 x 8, 256 x 6, 512 x 8, 16 or 32 with every
+    // item checked: W = 10, N = 1000, 256 energies 1.08 -> 1.02 ms, six W = 8 wires (402 to 3202
+    // outcomes) 7.3 -> 6.1 ms, W = 7, N = 427, 37 energies 0.049 -> 0.039 ms.
+    typedef void (*Build)(AliasArgs);
+    static const Build k128[8] = {
+        alias_build_kernel<128, 1, 1, kBias>, alias_build_kernel<128, 2, 1, kBias>,
+        alias_build_kernel<128, 3, 1, kBias>, alias_build_kernel<128, 4, 1, kBias>,
+        alias_build_kernel<128, 5, 1, kBias>, alias_build_kernel<128, 6, 1, kBias>,
+        alias_build_kernel<128, 7, 1, kBias>, alias_build_kernel<128, 8, 1, kBias>};
+    static const Build k256[2] = {alias_build_kernel<256, 5, 1, kBias>,
+                                  alias_build_kernel<256, 6, 1, kBias>};
+    static const Build k512[5] = {
+        alias_build_kernel<512, 4, 1, kBias>, alias_build_kernel<512, 5, 1, kBias>,
+        alias_build_kernel<512, 6, 1, kBias>, alias_build_kernel<512, 7, 1, kBias>,
+        alias_build_kernel<512, 8, 1, kBias>};
+    static const Build k512_2[4] = {
+        alias_build_kernel<512, 10, 2, kBias>, alias_build_kernel<512, 12, 2, kBias>,
+        alias_build_kernel<512, 14, 2, kBias>, alias_build_kernel<512, 16, 2, kBias>};
+    static const Build k512_4[4] = {
+        alias_build_kernel<512, 20, 4, kBias>, alias_build_kernel<512, 24, 4, kBias>,
+        alias_build_kernel<512, 28, 4, kBias>, alias_build_kernel<512, 32, 4, kBias>};
+    const int bt = n <= 1024 ? 128 : n <= 1536 ? 256 : 512;
+    const int items = (n + bt - 1) / bt;
+    const Build fn = bt == 128   ? k128[items - 1]
+                     : bt == 256 ? k256[items - 5]
+                     : items <= 8  ? k512[items - 4]
+                     : items <= 16 ? k512_2[(items - 9) / 2]
+                                   : k512_4[(items - 17) / 4];
     if (lds > 65536) {
         // rows beyond 6.5k outcomes need more than 64 KB of LDS per workgroup (gfx950: 160 KB)
         int dev = 0, per_block = 0, optin = 0;
@@ -673,21 +700,15 @@ static hipError_t launch_alias_rows(const mcnegf_kernel& k, const AliasArgs& a,
         }
         const int max_lds = optin > per_block ? optin : per_block;
         hipFuncAttributes fa;
-        if ((err = hipFuncGetAttributes(&fa, fns[shape])) != hipSuccess) return err;
+        if ((err = hipFuncGetAttributes(&fa, (const void*)fn)) != hipSuccess) return err;
         if (lds + fa.sharedSizeBytes > (size_t)max_lds) return hipErrorInvalidConfiguration;
-        err = hipFuncSetAttribute(fns[shape], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        err = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)lds);
         if (err != hipSuccess) return err;
     }
     {
         MCNEGF_TIMED(name, s);
-        const dim3 grid(n, k.nE), block(bts[shape]);
-        switch (shape) {
-            case 0: hipLaunchKernelGGL((alias_build_kernel<128, 8, kBias>), grid, block, lds, s, a); break;
-            case 1: hipLaunchKernelGGL((alias_build_kernel<256, 6, kBias>), grid, block, lds, s, a); break;
-            case 2: hipLaunchKernelGGL((alias_build_kernel<512, 8, kBias>), grid, block, lds, s, a); break;
-            case 3: hipLaunchKernelGGL((alias_build_kernel<512, 16, kBias>), grid, block, lds, s, a); break;
-            default: hipLaunchKernelGGL((alias_build_kernel<512, 32, kBias>), grid, block, lds, s, a); break;
-        }
+        hipLaunchKernelGGL(fn, dim3(n, k.nE), dim3(bt), lds, s, a);
     }
     return hipGetLastError();
 }
