@@ -94,27 +94,40 @@ hipError_t launch_mc_current(const mcnegf_kernel& k, uint32_t inject_lead, const
 // e0 scores c_p(e0) at its exit, so the exits at lead r with energy e give
 //   S[r][e] = sum_e0 w_e0 c_p(e0) hist[r][e0][e] / N_e0
 // (N_e0 the walkers injected at e0, truncated ones included); sum_e S[q][e] is the current of
-// the tallies.  One thread per (r, e); the sum over e0 runs in order.
+// the tallies.  A workgroup takes 16 entries of one lead: 16 threads per entry sum every 16th e0,
+// the partial sums are added in a fixed order (one thread per entry, a chain of nE loads, took
+// 135 us at 256 energies).
 __global__ void __launch_bounds__(256) spectrum_kernel(const int64_t* __restrict__ tallies,
                                                        const int64_t* __restrict__ hist,
                                                        const double* __restrict__ lead,
                                                        const double* __restrict__ weights,
                                                        int nE, uint32_t inject_lead,
                                                        double* __restrict__ S) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= 2 * nE) return;
-    const int r = idx / nE, e = idx % nE;
+    __shared__ double part[16][17];
+    const int r = blockIdx.y;
+    const int ce = threadIdx.x & 15, ch = threadIdx.x >> 4;
+    const int e = blockIdx.x * 16 + ce;
+    const int slot = inject_lead == 0 ? MCNEGF_LEAD_CL : MCNEGF_LEAD_CR;
     double acc = 0.0;
-    for (int e0 = 0; e0 < nE; ++e0) {
-        const int64_t* t = tallies + (size_t)e0 * MCNEGF_TALLY_N;
-        const int64_t nw = t[MCNEGF_TALLY_EXIT_L] + t[MCNEGF_TALLY_EXIT_R] + t[MCNEGF_TALLY_TRUNC];
-        const int64_t h = hist[((size_t)r * nE + e0) * nE + e];
-        if (nw <= 0 || h == 0) continue;
-        const double c = lead[(size_t)e0 * MCNEGF_LEAD_NTERMS +
-                              (inject_lead == 0 ? MCNEGF_LEAD_CL : MCNEGF_LEAD_CR)];
-        acc += weights[e0] * c / (double)nw * (double)h;
+    if (e < nE) {
+#pragma unroll 4
+        for (int e0 = ch; e0 < nE; e0 += 16) {
+            const int64_t* t = tallies + (size_t)e0 * MCNEGF_TALLY_N;
+            const int64_t nw =
+                t[MCNEGF_TALLY_EXIT_L] + t[MCNEGF_TALLY_EXIT_R] + t[MCNEGF_TALLY_TRUNC];
+            const int64_t h = hist[((size_t)r * nE + e0) * nE + e];
+            const double c = lead[(size_t)e0 * MCNEGF_LEAD_NTERMS + slot];
+            acc += nw > 0 && h != 0 ? weights[e0] * c / (double)nw * (double)h : 0.0;
+        }
     }
-    S[idx] = acc;
+    part[ch][ce] = acc;
+    __syncthreads();
+    if (threadIdx.x < 16 && e < nE) {
+        double sum = 0.0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum += part[i][ce];
+        S[(size_t)r * nE + e] = sum;
+    }
 }
 
 hipError_t launch_spectrum(const mcnegf_kernel& k, uint32_t inject_lead, const int64_t* tallies,
@@ -122,8 +135,8 @@ hipError_t launch_spectrum(const mcnegf_kernel& k, uint32_t inject_lead, const i
                            hipStream_t s) {
     {
         MCNEGF_TIMED("spectrum_kernel", s);
-        hipLaunchKernelGGL(spectrum_kernel, dim3((2 * k.nE + 255) / 256), dim3(256), 0, s,
-                           tallies, hist, k.lead, weights, k.nE, inject_lead, spectrum);
+        hipLaunchKernelGGL(spectrum_kernel, dim3((k.nE + 15) / 16, 2), dim3(256), 0, s, tallies,
+                           hist, k.lead, weights, k.nE, inject_lead, spectrum);
     }
     return hipGetLastError();
 }
