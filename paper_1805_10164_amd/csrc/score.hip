@@ -44,17 +44,26 @@ __device__ inline void block_matvec(double2 (&out)[W], const double2 (&in)[W], c
 }
 
 // Per energy: mu_s = n_s / A_ss (n_s = steps out of probe s, a column sum of the
-// outcome-major counts: threads over s read each row coalesced) into sv[0] ([chunk][2][ld]).
-__global__ void __launch_bounds__(256) score_prep_kernel(const uint32_t* __restrict__ counts,
-                                                         const double* __restrict__ Adiag, int N,
-                                                         int64_t ld, double* __restrict__ sv) {
+// outcome-major counts) into sv[0] ([chunk][2][ld]).  A workgroup takes 64 columns, each wavefront
+// every 16th row of them: with one thread walking a whole column too few reads were in flight
+// (N = 615, 48 energies: 239 -> 32 us).
+__global__ void __launch_bounds__(1024) score_prep_kernel(const uint32_t* __restrict__ counts,
+                                                          const double* __restrict__ Adiag, int N,
+                                                          int64_t ld, double* __restrict__ sv) {
+    __shared__ uint64_t part[16][64];
     const int e = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane;
     const int n = N + 2;
-    const uint32_t* C = counts + (size_t)e * n * n;
+    const uint32_t* C = counts + (size_t)e * n * n + min(i, N - 1);
     uint64_t out = 0;
-    for (int o = 0; o < n; ++o) out += C[(size_t)o * n + i];
+#pragma unroll 8
+    for (int o = wv; o < n; o += 16) out += C[(size_t)o * n];
+    part[wv][lane] = out;
+    __syncthreads();
+    if (threadIdx.x >= 64 || i >= N) return;
+#pragma unroll
+    for (int w = 1; w < 16; ++w) out += part[w][lane];
     const double a = Adiag[(size_t)e * N + i];
     sv[(size_t)e * 2 * ld + i] = out ? (double)out / a : 0.0;
 }
@@ -75,17 +84,80 @@ __global__ void __launch_bounds__(64) score_rowsum_kernel(const uint32_t* __rest
     if (threadIdx.x == 0) sv[(size_t)e * 2 * ld + ld + o] = (double)in;
 }
 
+// a's lower half and b's lower half side by side, summed with their upper halves: lanes below 32
+// get a's sums, the others b's (and the same by rows of 16 for rows16).
+__device__ inline double halves32(double a, double b) {
+    auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+__device__ inline double halves16(double a, double b) {
+    auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+template <int CTRL>
+__device__ inline double dpp_of(double v) {
+    return __hiloint2double(
+        __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true),
+        __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true));
+}
+
+// The wavefront's sums of v[r], r < W, by halving: each exchange sums two values into one (real
+// against imaginary part, then rows by the bits of r), so a value costs about two exchanges in
+// place of six.  out[i] of a lane is the part (lane >> 5) of row
+// 8 i + 4 ((lane >> 2) & 1) + 2 ((lane >> 3) & 1) + ((lane >> 4) & 1).
+template <int W>
+__device__ inline void wave_sums(double (&out)[(W + 7) / 8], const double2 (&v)[W], int lane) {
+    constexpr int W2 = (W + 1) / 2, W4 = (W + 3) / 4;
+    double a[W], b[W2], c[W4];
+#pragma unroll
+    for (int r = 0; r < W; ++r) a[r] = halves32(v[r].x, v[r].y);
+#pragma unroll
+    for (int r = 0; r < W2; ++r) b[r] = halves16(a[2 * r], 2 * r + 1 < W ? a[2 * r + 1] : 0.0);
+#pragma unroll
+    for (int r = 0; r < W4; ++r) {  // rotation by 8 of a row of 16
+        const double x = b[2 * r], y = 2 * r + 1 < W2 ? b[2 * r + 1] : 0.0;
+        const bool up = (lane & 8) != 0;
+        c[r] = (up ? y : x) + dpp_of<0x128>(up ? x : y);
+    }
+#pragma unroll
+    for (int r = 0; r < (W + 7) / 8; ++r) {  // mirror of a row's half, then the four lanes left
+        const double x = c[2 * r], y = 2 * r + 1 < W4 ? c[2 * r + 1] : 0.0;
+        const bool up = (lane & 4) != 0;
+        double s = (up ? y : x) + dpp_of<0x141>(up ? x : y);
+        s += dpp_of<0x4E>(s);  // quad_perm 2,3,0,1
+        s += dpp_of<0xB1>(s);  // quad_perm 1,0,3,2
+        out[r] = s;
+    }
+}
+
 // One lane per right-hand side: c < N is row c of Psi (its probe entries and the diagonal
 // term); c = N + a is the solve for R_a of lead p (a < W) or of lead q (a >= W).  The forward
 // sweep keeps y in Y[.][c]; the backward sweep stores z only for the lead rows, and the
 // wavefront sums G_mc z_m over its lanes c < N for every m, storing the sum in column 64 *
 // blockIdx.x of Y (lane 0's own column, whose y at row m it has already read).
+//
+// The two chains over the slices are serial and a case of a few dozen energies has one or two
+// wavefronts per CU, so what bounds it is the latency of each slice's loads.  None of them depends
+// on the chain: the slice's G entries, counts and y rows are loaded AHEAD slices early and its gL
+// block one slice early; the sums of a slice's rows share their exchanges.  W = 5, N = 615, 48
+// energies: 1.33 -> 0.41 ms, 2.9 TB/s of the 1.2 GB it moves.
+// Loads ahead cost registers: up to W = 12 two wavefronts per SIMD hold them, at W = 13 .. 16 they
+// would leave one (W = 16, N = 640, 128 energies: 1.79 ms with, 1.27 ms without, 1.54 ms before),
+// at W = 17 .. 24 one is left either way (W = 20, N = 800, 64 energies: 2.2 -> 1.43 ms) and above
+// that they no longer fit (W = 32, N = 960, 64 energies: 4.16 -> 3.37 ms without).
 template <int W>
-__global__ void __launch_bounds__(64) score_solve_kernel(
+__global__ void __launch_bounds__(64, W <= 16 ? 2 : 1) score_solve_kernel(
     const double2* __restrict__ gL, const double2* __restrict__ Gc,
     const uint32_t* __restrict__ counts, const double* __restrict__ sv,
     const double* __restrict__ wL, const double* __restrict__ wR, int L, double t, int64_t ld,
     int64_t ldY, uint32_t inject_lead, double2* __restrict__ Y) {
+    constexpr bool EARLY = W <= 12 || (W > 16 && W <= 24);
+    constexpr int AHEAD = W <= 4 ? 4 : (W <= 8 ? 2 : 1);
+    constexpr int NM = (W * W + 63) / 64;
     const int N = W * L;
     const int n = N + 2;
     const int NC = N + 2 * W;
@@ -104,89 +176,150 @@ __global__ void __launch_bounds__(64) score_solve_kernel(
     const int col = dense ? c : (valid ? (leadp ? sp + (c - N) : sq + (c - N - W)) : 0);
     const int cl = valid ? c : 0;  // column of Y that idle lanes read
     const bool has_dense = blockIdx.x * 64 < N;
-    const double2* Ge = Gc + (size_t)e * N * ld;
+    const bool has_lead = blockIdx.x * 64 + 63 >= N;
+    const double2* Ge = Gc + (size_t)e * N * ld + col;
     double2* Ye = Y + (size_t)e * N * ldY;
-    const uint32_t* Ce = counts + (size_t)e * n * n;
-    const double* wp = (inject_lead == 0 ? wL : wR) + (size_t)e * N;
-    const double* wq = (inject_lead == 0 ? wR : wL) + (size_t)e * N;
+    // the counts of the right-hand side's entries j: C[j][c], C[j][pr] (lead p) or C[qo][j]
+    // (lead q), and what divides them: |G_cj|^2 / 2, w_p(j) or w_q(j)
+    const uint32_t* Ce = counts + (size_t)e * n * n +
+                         (dense ? (size_t)c : (leadp ? (size_t)pr : (size_t)qo * n));
+    const size_t cstride = dense || leadp ? (size_t)n : 1;
+    const double* we = ((inject_lead == 0) == leadp ? wL : wR) + (size_t)e * N;
     const double mu = dense ? sv[(size_t)e * 2 * ld + c] : 0.0;
     const double2* gLe = gL + (size_t)e * L * W * W;
     lds_double* Ms = (lds_double*)Ms_raw;
     constexpr int BS = 2 * W * W;
-    auto stage = [&](int buf, int slice) {
+    double2 mreg[NM];  // the next slice's block of gL on its way to LDS
+    auto load_block = [&](int slice) {
 #pragma unroll
-        for (int i = tid; i < W * W; i += 64) {
-            const double2 v = gLe[(size_t)slice * W * W + i];
-            Ms[buf * BS + 2 * i] = v.x;
-            Ms[buf * BS + 2 * i + 1] = v.y;
+        for (int i = 0; i < NM; ++i) {
+            const int x = tid + 64 * i;
+            if (x < W * W) mreg[i] = gLe[(size_t)slice * W * W + x];
         }
     };
-    double2 y[W], z[W];
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            const int x = tid + 64 * i;
+            if (x < W * W) {
+                Ms[buf * BS + 2 * x] = mreg[i].x;
+                Ms[buf * BS + 2 * x + 1] = mreg[i].y;
+            }
+        }
+    };
+    double2 y[W], z[W], g[AHEAD][W];
+    // forward: slice k's entries of G, counts and lead weights in g[k % AHEAD] and its like
+    uint32_t cn[AHEAD][W];
+    double wd[AHEAD][W];
+    auto load_entry = [&](int u, int k, int r) {
+        const int j = k * W + r;
+        g[u][r] = Ge[(size_t)j * ld];  // G_{j,col} = G_{col,j}
+        cn[u][r] = Ce[(size_t)j * cstride];
+        wd[u][r] = has_lead ? we[j] : 1.0;
+    };
+    auto load_entries = [&](int u, int k) {
+#pragma unroll
+        for (int r = 0; r < W; ++r) load_entry(u, k, r);
+    };
 #pragma unroll
     for (int r = 0; r < W; ++r) y[r] = cmk(0.0, 0.0);
-    stage(0, 0);
-    for (int k = 0; k < L; ++k) {
-        __syncthreads();
-        const lds_double* cur = Ms + (k & 1) * BS;
-        if (k + 1 < L) stage((k + 1) & 1, k + 1);
+    load_block(0);
 #pragma unroll
-        for (int r = 0; r < W; ++r) {
-            const int j = k * W + r;
-            const double2 g = Ge[(size_t)j * ld + col];  // G_{j,col} = G_{col,j}
-            double2 v;
-            if (dense) {
-                // 2 C[j][c] / G_cj, and -2i mu_c on the diagonal
-                const uint32_t cn = Ce[(size_t)j * n + c];
-                const double inv = cn ? 2.0 * (double)cn / cabs2(g) : 0.0;
-                v = cmk(inv * g.x, -inv * g.y);
-                if (j == c) v.y -= 2.0 * mu;
-            } else {
-                // k_j conj(G_{j,s_a}): k_j = C[j][pr] / w_p(j) (lead p) or C[qo][j] / w_q(j)
-                const uint32_t cn = leadp ? Ce[(size_t)j * n + pr] : Ce[(size_t)qo * n + j];
-                const double w = leadp ? wp[j] : wq[j];
-                const double kk = (valid && cn) ? (double)cn / w : 0.0;
-                v = cmk(kk * g.x, -kk * g.y);
+    for (int u = 0; u < AHEAD; ++u)
+        if (EARLY && u < L) load_entries(u, u);
+    stage(0);
+    if (L > 1) load_block(1);
+    for (int k0 = 0; k0 < L; k0 += AHEAD) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int k = k0 + u;
+            if (k >= L) break;
+            __syncthreads();
+            if (k + 1 < L) stage((k + 1) & 1);
+            if (k + 2 < L) load_block(k + 2);
+#pragma unroll
+            for (int r = 0; r < W; ++r) {
+                const int j = k * W + r;
+                if (!EARLY) load_entry(u, k, r);
+                const double2 gj = g[u][r];
+                // dense: 2 C / G_cj, and -2i mu_c on the diagonal; leads: k_j conj(G_{j,s_a})
+                const double num = dense ? 2.0 * (double)cn[u][r] : (double)cn[u][r];
+                const double den = dense ? cabs2(gj) : wd[u][r];
+                const double q = valid && cn[u][r] ? num / den : 0.0;
+                double2 v = cmk(q * gj.x, -q * gj.y);
+                if (dense && j == c) v.y -= 2.0 * mu;
+                z[r] = cmk(v.x - t * y[r].x, v.y - t * y[r].y);
+                if (!EARLY) __builtin_amdgcn_sched_barrier(0);  // one row's registers at a time
             }
-            z[r] = cmk(v.x - t * y[r].x, v.y - t * y[r].y);
-        }
-        block_matvec<W>(y, z, cur);
-        if (valid) {
+            if (EARLY && k + AHEAD < L) load_entries(u, k + AHEAD);
+            __builtin_amdgcn_sched_barrier(0);
+            block_matvec<W>(y, z, Ms + (k & 1) * BS);
+            if (valid) {
 #pragma unroll
-            for (int r = 0; r < W; ++r) Ye[(size_t)(k * W + r) * ldY + c] = y[r];
+                for (int r = 0; r < W; ++r) Ye[(size_t)(k * W + r) * ldY + c] = y[r];
+            }
         }
     }
-    // backward: y holds y_{L-1} = z_{L-1}
+    // backward: y holds y_{L-1} = z_{L-1}; step i takes slice k = L - 1 - i, its entries of G in
+    // g[i % AHEAD] and its y (from slice L - 2 on) in yk
+    double2 yk[AHEAD][W];
+    auto load_back = [&](int u, int k) {
+#pragma unroll
+        for (int r = 0; r < W; ++r) {
+            if (has_dense) g[u][r] = Ge[(size_t)(k * W + r) * ld];
+            yk[u][r] = Ye[(size_t)(k * W + r) * ldY + cl];
+        }
+    };
     __syncthreads();
-    if (L > 1) stage(0, L - 2);
-    for (int k = L - 1; k >= 0; --k) {
-        if (k < L - 1) {
-            const int j = L - 2 - k;
-            __syncthreads();
-            const lds_double* cur = Ms + (j & 1) * BS;
-            if (k > 0) stage((j + 1) & 1, k - 1);
-            block_matvec<W>(z, y, cur);
+    if (L > 1) load_block(L - 2);
 #pragma unroll
-            for (int r = 0; r < W; ++r) {
-                const double2 yk = Ye[(size_t)(k * W + r) * ldY + cl];
-                y[r] = cmk(fma(-t, z[r].x, yk.x), fma(-t, z[r].y, yk.y));
-            }
-        }
-        if (valid && !dense) {
+    for (int u = 0; u < AHEAD; ++u)
+        if (EARLY && u < L) load_back(u, L - 1 - u);
+    if (L > 1) stage((L - 2) & 1);
+    if (L > 2) load_block(L - 3);
+    for (int i0 = 0; i0 < L; i0 += AHEAD) {
 #pragma unroll
-            for (int r = 0; r < W; ++r) Ye[(size_t)(k * W + r) * ldY + c] = y[r];
-        }
-        if (has_dense) {  // uniform: the wavefront's sums over its right-hand sides c < N
+        for (int u = 0; u < AHEAD; ++u) {
+            const int k = L - 1 - i0 - u;
+            if (k < 0) break;
+            double2 gk[EARLY ? W : 1];
+            if (k < L - 1) {
+                __syncthreads();
+                if (k > 0) stage((k + 1) & 1);
+                if (k > 1) load_block(k - 2);
+                block_matvec<W>(z, y, Ms + (k & 1) * BS);
 #pragma unroll
-            for (int r = 0; r < W; ++r) {
-                const int m = k * W + r;
-                double2 v = cmk(0.0, 0.0);
-                if (dense) v = cmul(Ge[(size_t)m * ld + c], y[r]);
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) {
-                    v.x += __shfl_xor(v.x, o, 64);
-                    v.y += __shfl_xor(v.y, o, 64);
+                for (int r = 0; r < W; ++r) {
+                    if (!EARLY) yk[u][r] = Ye[(size_t)(k * W + r) * ldY + cl];
+                    y[r] = cmk(fma(-t, z[r].x, yk[u][r].x), fma(-t, z[r].y, yk[u][r].y));
+                    if (!EARLY) __builtin_amdgcn_sched_barrier(0);
                 }
-                if (tid == 0) Ye[(size_t)m * ldY + 64 * blockIdx.x] = v;
+            }
+#pragma unroll
+            for (int r = 0; r < (EARLY ? W : 0); ++r) gk[r] = g[u][r];
+            if (EARLY && k - AHEAD >= 0) load_back(u, k - AHEAD);
+            __builtin_amdgcn_sched_barrier(0);
+            if (valid && !dense) {
+#pragma unroll
+                for (int r = 0; r < W; ++r) Ye[(size_t)(k * W + r) * ldY + c] = y[r];
+            }
+            if (has_dense) {  // uniform: the wavefront's sums over its right-hand sides c < N
+                double sum[(W + 7) / 8];
+#pragma unroll
+                for (int r = 0; r < W; ++r) {
+                    const double2 v = cmul(EARLY ? gk[EARLY ? r : 0] : Ge[(size_t)(k * W + r) * ld], y[r]);
+                    z[r] = cmk(dense ? v.x : 0.0, dense ? v.y : 0.0);
+                    if (!EARLY) __builtin_amdgcn_sched_barrier(0);
+                }
+                wave_sums<W>(sum, z, tid);
+                const int row = 4 * ((tid >> 2) & 1) + 2 * ((tid >> 3) & 1) + ((tid >> 4) & 1);
+#pragma unroll
+                for (int i = 0; i < (W + 7) / 8; ++i)
+                    if ((tid & 3) == 0 && 8 * i + row < W) {
+                        double* to = reinterpret_cast<double*>(
+                            Ye + (size_t)(k * W + 8 * i + row) * ldY + 64 * blockIdx.x);
+                        to[tid >> 5] = sum[i];
+                    }
             }
         }
     }
@@ -279,7 +412,7 @@ static hipError_t launch_score_w(const mcnegf_kernel& k, const GradBuffers& gb,
                                  uint32_t inject_lead, hipStream_t s) {
     {
         MCNEGF_TIMED("score_prep_kernel", s);
-        hipLaunchKernelGGL(score_prep_kernel, dim3((k.N + 255) / 256, k.nE), dim3(256), 0, s,
+        hipLaunchKernelGGL(score_prep_kernel, dim3((k.N + 63) / 64, k.nE), dim3(1024), 0, s,
                            counts, k.Adiag, k.N, gb.ld, gb.xl);
     }
     hipError_t err = hipGetLastError();
