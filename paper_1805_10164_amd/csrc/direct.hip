@@ -347,7 +347,7 @@ __global__ void direct_prep_kernel(const double* __restrict__ P, const double* _
 // Measured against one workgroup per energy going left-looking through 64-column panels (split
 // over workgroups by panel rows with few energies), ms per factorization:
 //   N = 16000, 8 energies    418 -> 174  (63 TFLOP/s)     N = 4000, 64 energies   39.4 -> 27.3
-//   N = 3200, 128 energies  35.3 -> 29.3                  N = 1000, 256 energies  2.85 -> 2.83
+//   N = 3200, 128 energies  35.3 -> 29.3                  N = 1000, 256 energies  2.85 -> 2.60
 // (the split formed each diagonal block, a product over all previous columns, in every
 // workgroup, and the factor's serial chain of pivots took 24 us per 64 columns).
 //
@@ -361,6 +361,7 @@ __global__ void direct_prep_kernel(const double* __restrict__ P, const double* _
 // column permutation leaves unchanged, and the two bordered rows enter only through their dot
 // product, which it leaves unchanged too.
 typedef double dmfma4 __attribute__((ext_vector_type(4)));
+typedef double dmfma4u __attribute__((ext_vector_type(4), aligned(8)));  // four of any row
 typedef double dvec2 __attribute__((ext_vector_type(2)));
 
 constexpr int CH_NB = 128;            // panel width
@@ -638,14 +639,18 @@ __device__ inline int xcd_contiguous(int total) {
 // Rows below a full panel: V L_JJ^{-T}, two 16-row tiles per wavefront at a time, `rows` times.
 // An odd panel (UPD) first takes the product with the previous panel's 128 columns: its rows
 // and the panel's come from L2, and V is read once instead of being written by a launch of its
-// own and read again.
+// own and read again.  The steps of a tile are a serial chain of products, so its reads are what
+// can be hidden: V's entries are loaded a tile ahead and before the stores of the tile at hand,
+// the product's operands a block column ahead (N = 1000, 256 energies: the seven launches
+// 1022 -> 809 us, the first 240 -> 152 us at 3.0 TB/s).
 constexpr int CH_SOLVE_WAVES = 4;
 constexpr int CH_SOLVE_ROWS = 32 * CH_SOLVE_WAVES;  // rows per workgroup and pass
 
 template <bool UPD>
 __global__ void __launch_bounds__(64 * CH_SOLVE_WAVES, 2) cholesky_solve_kernel(CholArgs a) {
-    __shared__ double S_raw[CH_NBLK * 256];
+    __shared__ double S_raw[CH_NBLK * 256 + CH_NB];
     lds_double* S = (lds_double*)S_raw;
+    lds_double* us = S + CH_NBLK * 256;  // the scales of the panel's columns
     const int idx = xcd_contiguous(a.nE * a.tiles);
     if (idx >= a.nE * a.tiles) return;
     const int e = idx / a.tiles, part = idx - e * a.tiles;
@@ -667,41 +672,97 @@ __global__ void __launch_bounds__(64 * CH_SOLVE_WAVES, 2) cholesky_solve_kernel(
         if (kb == mb) z_home(mb, mb, kb);
         lds_store4(S + q * 256 + at, load4(Ld + (size_t)(16 * mb + n) * ld + 16 * kb + 4 * g));
     }
+    // a full panel's columns are below N, and no row below it meets the diagonal there: an entry is
+    // one of V's (J >= 2), a scaled one of P or one of a bordered row, 32 bytes of one row each way
+    const bool orig = a.J <= 1;
+    if (threadIdx.x < CH_NB) us[threadIdx.x] = orig ? ve[c0 + threadIdx.x] : 0.0;
     __syncthreads();
-    for (int t = 0; t < a.rows; ++t) {
-        const int row0 = c0 + CH_NB + 32 * ((part * a.rows + t) * CH_SOLVE_WAVES + wave);
-        if (row0 >= R) break;
+    auto load_v = [&](dmfma4 (&v)[CH_SB], double& ui, int row) {
+        const int i = min(row + n, R - 1);
+        const int si = min(ch_site(i), a.N - 1);
+        const double* src = !orig ? Le + (size_t)i * ld
+                            : i < a.Np ? Pe + (size_t)si * ld : ve + (size_t)(i - a.Np + 1) * a.N;
+        src += c0 + 4 * g;
+        ui = ve[si];
+#pragma unroll
+        for (int kb = 0; kb < CH_SB; ++kb) {
+            const dmfma4u x = *reinterpret_cast<const dmfma4u*>(src + 16 * kb);
+            v[kb] = dmfma4{x[0], x[1], x[2], x[3]};
+        }
+    };
+    auto entry = [&](dmfma4 v, double ui, int row, int kb) {
+        const int i = min(row + n, R - 1);
+        if (!orig || i >= a.Np) return v;
+        const dmfma4 uj = lds_load4(us + 16 * kb + 4 * g);
+        dmfma4 out;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out[r] = ch_site(i) < a.N ? -ui * uj[r] * v[r] : 0.0;
+        return out;
+    };
+    const int pass = CH_SOLVE_ROWS;
+    const int first = c0 + CH_NB + part * a.rows * pass + 32 * wave;
+    const int last = min(first + (a.rows - 1) * pass + 32, R);
+    // The loads of a tile's entries are issued before the stores of the tile before it: loads
+    // and stores are counted in order, and behind the stores they would wait for those too.
+    dmfma4 v[CH_SB];
+    double ui = 0.0;
+    if (!UPD) {
+        if (first < last) load_v(v, ui, first);
+        for (int row = first; row < last; row += (row - first) % pass ? pass - 16 : 16) {
+            dmfma4 y[CH_SB];
+#pragma unroll
+            for (int kb = 0; kb < CH_SB; ++kb) y[kb] = entry(v[kb], ui, row, kb);
+            __builtin_amdgcn_sched_barrier(0);
+            const int next = row + ((row - first) % pass ? pass - 16 : 16);
+            if (next < last) load_v(v, ui, next);
+            __builtin_amdgcn_sched_barrier(0);
+            panel_solve(S, y, CH_SB, n, g);
+            if (row + n < R) {
+                double* dst = Le + (size_t)(row + n) * ld + c0 + 4 * g;
+#pragma unroll
+                for (int kb = 0; kb < CH_SB; ++kb) store4(dst + 16 * kb, y[kb]);
+            }
+        }
+        return;
+    }
+    for (int row0 = first; row0 < last; row0 += pass) {
         dmfma4 y[2][CH_SB];
         double* dst[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
             dst[h] = Le + (size_t)min(row0 + 16 * h + n, R - 1) * ld + c0 + 4 * g;
-        if (UPD) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int kb = 0; kb < CH_SB; ++kb) y[h][kb] = dmfma4{0.0, 0.0, 0.0, 0.0};
-            const double* xc = Ld + (size_t)n * ld + 4 * g - CH_NB;
-            for (int k = 0; k < CH_SB; ++k) {
-                const dmfma4 x0 = load4(dst[0] - CH_NB + 16 * k);
-                const dmfma4 x1 = load4(dst[1] - CH_NB + 16 * k);
+            for (int kb = 0; kb < CH_SB; ++kb) y[h][kb] = dmfma4{0.0, 0.0, 0.0, 0.0};
+        const double* xc = Ld + (size_t)n * ld + 4 * g - CH_NB;
+        // the operands of block column k + 1 take the place of those of k as they are used
+        dmfma4 x0 = load4(dst[0] - CH_NB), x1 = load4(dst[1] - CH_NB);
 #pragma unroll
-                for (int kb = 0; kb < CH_SB; ++kb) {
-                    const dmfma4 c = load4(xc + (size_t)(16 * kb) * ld + 16 * k);
-                    y[0][kb] = mfma16(c, x0, y[0][kb]);
-                    y[1][kb] = mfma16(c, x1, y[1][kb]);
-                }
-            }
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            __builtin_amdgcn_sched_barrier(0);  // one tile's entries of V at a time (registers)
+        for (int kb = 0; kb < CH_SB; ++kb) v[kb] = load4(xc + (size_t)(16 * kb) * ld);
+        for (int k = 0; k < CH_SB; ++k) {
+            const int kn = 16 * min(k + 1, CH_SB - 1);
+            const dmfma4 x0n = load4(dst[0] - CH_NB + kn), x1n = load4(dst[1] - CH_NB + kn);
 #pragma unroll
             for (int kb = 0; kb < CH_SB; ++kb) {
-                const dmfma4 v = a.J <= 1 ? aorig4(a, Pe, ve, row0 + 16 * h + n, c0 + 16 * kb, g)
-                                          : load4(dst[h] + 16 * kb);
-                y[h][kb] = UPD ? v - y[h][kb] : v;
+                y[0][kb] = mfma16(v[kb], x0, y[0][kb]);
+                y[1][kb] = mfma16(v[kb], x1, y[1][kb]);
+                __builtin_amdgcn_sched_barrier(0);
+                v[kb] = load4(xc + (size_t)(16 * kb) * ld + kn);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            x0 = x0n;
+            x1 = x1n;
+        }
+        load_v(v, ui, row0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int kb = 0; kb < CH_SB; ++kb)
+                y[h][kb] = entry(v[kb], ui, row0 + 16 * h, kb) - y[h][kb];
+            __builtin_amdgcn_sched_barrier(0);
+            if (h == 0) load_v(v, ui, row0 + 16);
+            __builtin_amdgcn_sched_barrier(0);
             panel_solve(S, y[h], CH_SB, n, g);
             if (row0 + 16 * h + n < R) {
 #pragma unroll
