@@ -346,8 +346,8 @@ __global__ void direct_prep_kernel(const double* __restrict__ P, const double* _
 // The launch boundaries order the steps; no workgroup waits for another.
 // Measured against one workgroup per energy going left-looking through 64-column panels (split
 // over workgroups by panel rows with few energies), ms per factorization:
-//   N = 16000, 8 energies    418 -> 174  (63 TFLOP/s)     N = 4000, 64 energies   39.4 -> 27.3
-//   N = 3200, 128 energies  35.3 -> 29.3                  N = 1000, 256 energies  2.85 -> 2.60
+//   N = 16000, 8 energies    418 -> 171  (64 TFLOP/s)     N = 4000, 64 energies   39.4 -> 26.2
+//   N = 3200, 128 energies  35.3 -> 28.2                  N = 1000, 256 energies  2.85 -> 2.36
 // (the split formed each diagonal block, a product over all previous columns, in every
 // workgroup, and the factor's serial chain of pivots took 24 us per 64 columns).
 //
@@ -776,10 +776,11 @@ __global__ void __launch_bounds__(64 * CH_SOLVE_WAVES, 2) cholesky_solve_kernel(
 // accumulators (16 F x 16 F entries) each.  A 16x16x4 product occupies a SIMD for 64 clocks,
 // so a 128 x 128 tile needs 16 KB of operands per 8 columns and 4096 clocks: bandwidth is not
 // short, latency is.  The 8-column steps are staged in LDS (double-buffered, one barrier per
-// step) from registers loaded four steps ahead; two workgroups share a CU.  In a step lane group g takes the
-// positions 2 g, 2 g + 1 of both operands (the same permutation of the contracted columns on
-// both sides); a staged row is 64 bytes, its 16-byte pieces swizzled by the row so that eight
-// rows spread over all banks.
+// step) from registers loaded four steps ahead; two workgroups share a CU (four of 64 x 64, which
+// need twice the operands but are less often all at their reads and writes of V at once; the
+// launch takes the one that is faster).  In a step lane group g takes the positions 2 g, 2 g + 1
+// of both operands (the same permutation of the contracted columns on both sides); a staged row
+// is 64 bytes, its 16-byte pieces swizzled by the row so that eight rows spread over all banks.
 template <int F>
 __global__ void __launch_bounds__(256, F == 4 ? 2 : 4) cholesky_update_kernel(CholArgs a) {
     constexpr int TS = 32 * F;  // tile side
@@ -908,17 +909,32 @@ __global__ void __launch_bounds__(256, F == 4 ? 2 : 4) cholesky_update_kernel(Ch
     const bool first = a.J + 1 == a.m;
     const double* Pe = a.P + (size_t)e * a.N * ld;
     const double* ve = a.vec + (size_t)e * 4 * a.N;
-#pragma unroll
-    for (int tb = 0; tb < F; ++tb)
+    // one row of blocks is loaded before the one ahead of it is stored (loads behind stores wait
+    // for them)
+    dmfma4 v[2][F];
+    auto load_row = [&](int tb) {
+        const int row = min(i0 + 16 * tb + n, R - 1);
 #pragma unroll
         for (int cb = 0; cb < F; ++cb) {
-            const int row = i0 + 16 * tb + n, col = j0 + 16 * cb;
-            if (row < R && col < Np) {
-                double* at = Le + (size_t)row * ld + col + 4 * g;
-                const dmfma4 v = first ? aorig4(a, Pe, ve, row, col, g) : load4(at);
-                store4(at, v - acc[tb][cb]);
-            }
+            const int col = min(j0 + 16 * cb, Np - 16);
+            v[tb & 1][cb] = first ? aorig4(a, Pe, ve, row, col, g)
+                                  : load4(Le + (size_t)row * ld + col + 4 * g);
         }
+    };
+    load_row(0);
+#pragma unroll
+    for (int tb = 0; tb < F; ++tb) {
+        if (tb + 1 < F) load_row(tb + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const int row = i0 + 16 * tb + n;
+#pragma unroll
+        for (int cb = 0; cb < F; ++cb) {
+            const int col = j0 + 16 * cb;
+            if (row < R && col < Np)
+                store4(Le + (size_t)row * ld + col + 4 * g, v[tb & 1][cb] - acc[tb][cb]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 // T_k = T_qp + (row Np of L) . (row Np + 1 of L) after a factorization in several launches
@@ -981,7 +997,12 @@ static hipError_t factorize(CholArgs a, int cus, hipStream_t s) {
         else hipLaunchKernelGGL(cholesky_solve_kernel<false>, grid(), block, 0, s, a);
         if ((err = hipGetLastError()) != hipSuccess) return err;
         if ((J & 1) == 0) continue;
-        // update of the next m panels: 128 x 128 tiles while they fill the chip, else 64 x 64
+        // update of the next m panels.  Tiles of 64 x 64 leave four workgroups on a CU whose
+        // reads and writes of V overlap the others' products: with K = 128 m = 256 or 512
+        // columns they are ahead of 128 x 128 (N = 1000, 256 energies: 561 -> 481 and 800 ->
+        // 675 us).  From K = 1024 the larger tiles multiply 4 .. 7 % faster (N = 16000, 8
+        // energies, K = 2048: 13.8 -> 12.6 ms) unless their rounded edges cost more than that
+        // (N = 4000, 64 energies, K = 2048: 8.1 ms with 64, 8.8 with 128) or they are too few.
         a.m = (J + 1) & -(J + 1);
         const int c1 = (J + 1) * CH_NB;
         const int wide = std::min(a.m * CH_NB, a.Np - c1);
@@ -989,8 +1010,9 @@ static hipError_t factorize(CholArgs a, int cus, hipStream_t s) {
             const int nct = (wide + side - 1) / side, nrt = (R - c1 + side - 1) / side;
             return nct * (nct + 1) / 2 + (nrt - nct) * nct;
         };
-        const bool big = (int64_t)tiles(128) * a.nE >= cus;
-        a.tiles = tiles(big ? 128 : 64);
+        const int64_t t128 = tiles(128), t64 = tiles(64);
+        const bool big = a.m >= 8 && t128 * a.nE >= cus && 100 * t128 <= 26 * t64;
+        a.tiles = (int)(big ? t128 : t64);
         if (big) hipLaunchKernelGGL(cholesky_update_kernel<4>, grid(), dim3(256), 0, s, a);
         else hipLaunchKernelGGL(cholesky_update_kernel<2>, grid(), dim3(256), 0, s, a);
         if ((err = hipGetLastError()) != hipSuccess) return err;

@@ -12,10 +12,10 @@ from paper_1805_10164_amd import mcnegf as M
 pytestmark = pytest.mark.gpu
 
 # (W, L, energies): N + padding = 16, 16, 32, 112, 128, 128, 144, 256, 272, 384, 400, 528, 656,
-# 896; the last two have enough tiles for 128 x 128 ones
+# 896; 400 and 528 with many energies; 3568, whose update of eight panels has 128 x 128 tiles
 CASES = [(3, 5, 2), (2, 8, 2), (1, 17, 2), (2, 56, 2), (1, 127, 2), (4, 32, 2), (3, 43, 2),
          (8, 32, 2), (1, 257, 2), (6, 64, 2), (5, 79, 3), (3, 171, 2), (16, 41, 2), (7, 128, 2),
-         (4, 100, 96), (11, 48, 61)]
+         (4, 100, 96), (11, 48, 61), (16, 223, 2)]
 
 
 @pytest.mark.parametrize("W,L,nE", CASES)
