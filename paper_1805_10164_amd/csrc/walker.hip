@@ -392,13 +392,20 @@ constexpr int kWalkSlots = 3;
 hipError_t launch_walk(const mcnegf_kernel& k, uint64_t seed, uint32_t tag, uint32_t walker_begin,
                        uint32_t n_walkers, uint32_t max_steps, int64_t* tallies, hipStream_t s) {
     if (n_walkers == 0) return hipSuccess;
-    // One launch per round of kXcds * kEnergiesPerXcd energies: a kernel boundary keeps the
+    // One launch per round of kXcds * per_xcd energies: a kernel boundary keeps the
     // wavefronts of an XCD on the same energies, whose tables then stay in that XCD's L2
-    // (without it, wavefronts drift apart over many energies and the L2 thrashes).  Fewer than
-    // kXcds energies go in one launch in a single group.
+    // (without it, wavefronts drift apart over many energies and the L2 thrashes): four
+    // energies, or as many more (up to 16) as half the L2 holds the packed tables of (the chain
+    // of 50 sites, 1e5 walkers: 64 energies 117 us in two launches -> 95 in one, 256 energies
+    // 449 us in eight -> 292 in two).  Fewer than kXcds energies go in one launch in a single
+    // group.
     constexpr uint32_t kXcds = 8;
-    constexpr uint32_t kEnergiesPerXcd = 4;
-    constexpr uint32_t kMaxEnergiesPerLaunch = kXcds * kEnergiesPerXcd;
+    constexpr uint32_t kMinPerXcd = 4, kMaxPerXcd = 16;
+    constexpr uint64_t kTableBytesPerXcd = 2u << 20;
+    const uint64_t table_bytes = (uint64_t)k.n_out * (uint64_t)k.alias_pitch * 4;
+    const uint32_t per_xcd = (uint32_t)std::min<uint64_t>(
+        std::max<uint64_t>(kTableBytesPerXcd / table_bytes, kMinPerXcd), kMaxPerXcd);
+    const uint32_t max_energies = kXcds * per_xcd;
     const void* fn = (const void*)walk_kernel<kWalkSlots>;
     int dev = 0, cus = 0;
     hipError_t err;
@@ -409,15 +416,15 @@ hipError_t launch_walk(const mcnegf_kernel& k, uint64_t seed, uint32_t tag, uint
     // A workgroup copies the injection rows of its group's energies into LDS (a walk's first
     // step then reads LDS, not memory) while they take at most kInjectLdsBytes.
     constexpr size_t kInjectLdsBytes = 32768;
-    const size_t lds = (size_t)kMaxEnergiesPerLaunch * MCNEGF_TALLY_N * 8 + kInjectLdsBytes;
+    const size_t lds = (size_t)max_energies * MCNEGF_TALLY_N * 8 + kInjectLdsBytes;
     // persistent grid: no more workgroups than can be resident at once
     int per_cu = 0;
     if ((err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, lds)) != hipSuccess)
         return err;
     const uint32_t max_blocks = (uint32_t)(per_cu < 1 ? 1 : per_cu) * (uint32_t)cus;
-    for (uint32_t e_off = 0; e_off < (uint32_t)k.nE; e_off += kMaxEnergiesPerLaunch) {
+    for (uint32_t e_off = 0; e_off < (uint32_t)k.nE; e_off += max_energies) {
         WalkArgs A;
-        const uint32_t nE = min((uint32_t)k.nE - e_off, kMaxEnergiesPerLaunch);
+        const uint32_t nE = min((uint32_t)k.nE - e_off, max_energies);
         A.table_stride = (int64_t)k.n_out * k.alias_pitch;
         A.tables = k.alias + (size_t)e_off * A.table_stride;
         A.lows = k.alias_lo + (size_t)e_off * A.table_stride;
