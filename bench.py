@@ -169,7 +169,7 @@ def kernel_work(name, wl, walk_steps):
         # factorization N^3/3 plus the two forward substitutions of the bordered rows, 2 N^2
         return "mfma", nE * (N ** 3 / 3.0 + 2.0 * N * N) / 1e12, "TFLOP"
     if name == "fullinv_kernel":
-        # two sweeps per column slice: L*(L-1) complex W x W block products per energy
+        # all blocks of G: L*(L-1) complex W x W block products per energy (the kernel needs half)
         return "alu", nE * 8.0 * W ** 3 * wl.L * (wl.L - 1) / 1e12, "TFLOP"
     if name == "alias_build_kernel":
         # read gamma_i |G_ji|^2 rows and write one 4-byte entry plus 2 low threshold bytes per outcome
@@ -182,6 +182,8 @@ def roofline(name, wl, ms_per_launch, walk_steps):
     if w is None:
         return None
     bound, amount, unit = w
+    if name == "fullinv_kernel":
+        amount *= 0.5  # G = G^T: the blocks on and below the diagonal only
     if unit == "GB":
         achieved = amount / (ms_per_launch * 1e-3)
         r = {"kernel": name, "bound": bound, "achieved": achieved, "peak": HBM_PEAK_GBS,
@@ -285,11 +287,11 @@ def add_traffic_rate(roof):
 
 def grad_work(wl: inputs.Workload):
     """Algorithmic work of one adjoint_solve_kernel launch (all energies): HBM bytes (G read
-    in both sweeps, the forward results written and read back) and FP64 flops (two complex
-    W x W block products per slice for N + W right-hand sides)."""
+    once) and FP64 flops (two complex W x W block products per slice, one for each forward
+    elimination, for N columns)."""
     N, W, nE = wl.N, wl.W, wl.n_energies
-    nbytes = nE * (2.0 * 16 * N * N + 2.0 * 16 * N * (N + W))
-    flops = nE * (N + W) * 2.0 * wl.L * 8.0 * W * W
+    nbytes = nE * 16.0 * N * N
+    flops = nE * N * 2.0 * wl.L * 8.0 * W * W
     return nbytes, flops
 
 
@@ -785,8 +787,7 @@ def scale_bench(torch, dev, warmup, with_cpu, seed, timed_batches=None, fp32=Tru
     for _ in range(max(1, warmup)):
         one_batch(0)
     torch.cuda.synchronize()
-    # one timing window per batch: a batch launches about 270 kernels (the factorization of
-    # a 16000-row system is one launch per 64-column block) and a window records 512
+    # one timing window per batch: a window records 512 launches
     records = []
     flags = 0
     t0 = time.perf_counter()
@@ -810,7 +811,7 @@ def scale_bench(torch, dev, warmup, with_cpu, seed, timed_batches=None, fp32=Tru
     chol_ms = per_kernel["cholesky_kernel"]["ms_per_batch"]
     chol_flop = nE * (wl.N ** 3 / 3.0 + 2.0 * wl.N * wl.N)
     fi_ms = per_kernel["fullinv_kernel"]["ms_per_launch"]
-    fi_flop = nE * 8.0 * wl.W ** 3 * wl.L * (wl.L - 1)
+    fi_flop = nE * 4.0 * wl.W ** 3 * wl.L * (wl.L - 1)  # G = G^T: half of G's blocks
     I_mc, s_mc = float(o[:, 0, 0].sum()), float(np.sqrt(np.sum(o[:, 0, 1] ** 2)))
     I_d = float(o[:, 1, 0].sum())
 
@@ -846,7 +847,7 @@ def scale_bench(torch, dev, warmup, with_cpu, seed, timed_batches=None, fp32=Tru
         "per_kernel": per_kernel,
         "rooflines": {
             "walk_kernel": walk_roof,
-            # the factorization is one launch per 64-column block: figures per batch
+            # the factorization is many launches under one timer record: figures per batch
             "cholesky_kernel": {"bound": "mfma", "achieved": chol_flop / 1e12 / (chol_ms * 1e-3),
                                 "peak": FP64_VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
                                 "frac": chol_flop / 1e12 / (chol_ms * 1e-3) /
