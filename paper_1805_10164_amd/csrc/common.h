@@ -148,7 +148,6 @@ struct LaunchTimer {
 #define MCNEGF_TIMED(name, stream) ::mcnegf::LaunchTimer mcnegf_timer_(name, stream)
 
 // ---- launchers (each defined next to its kernel) ----------------------------------------
-hipError_t launch_clear_status(uint32_t* status, uint32_t* counters, hipStream_t s);
 hipError_t launch_lead_sigma(const mcnegf_kernel& k, double gamma_l, double delta,
                              hipStream_t s);
 hipError_t launch_rgf(const mcnegf_kernel& k, const double* onsite, hipStream_t s);
@@ -202,10 +201,10 @@ hipError_t launch_walk(const mcnegf_kernel& k, uint64_t seed, uint32_t tag,
                        int64_t* tallies, hipStream_t s);
 hipError_t launch_mc_current(const mcnegf_kernel& k, uint32_t inject_lead,
                              const int64_t* tallies, const double* weights, double* T,
-                             double* sigmaT, hipStream_t s);
+                             double* sigmaT, double* I_sigma, hipStream_t s);
 hipError_t launch_direct_current(const mcnegf_kernel& k, uint32_t inject_lead,
                                  const double* weights, double* T, double* sigmaT,
-                                 hipStream_t s);
+                                 double* I_sigma, hipStream_t s);
 hipError_t launch_walk_batch(const mcnegf_batch& b, uint64_t seed, uint32_t walker_begin,
                              uint32_t n_walkers, uint32_t max_steps, const mcnegf_walk_config& c,
                              int64_t* tally_override, hipStream_t s);

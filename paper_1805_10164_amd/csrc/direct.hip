@@ -33,59 +33,75 @@ __device__ inline double block_reduce256(double v, double* red) {
     return r;
 }
 
-// Weighted sums over energies (one block, fixed order): out[0] = sum w T, out[1] = sum w^2 s^2.
+// The weighted sums over energies of a workgroup of 256 (fixed order): reduce[0] = sum w T,
+// reduce[1] = sum w^2 s^2, and I, sigma_I for the caller if I_sigma is given.
+__device__ inline void store_current(double a, double b, double* red, double* __restrict__ reduce,
+                                     double* __restrict__ I_sigma) {
+    a = block_reduce256(a, red);
+    b = block_reduce256(b, red);
+    if (threadIdx.x == 0) {
+        reduce[0] = a;
+        reduce[1] = b;
+        if (I_sigma) {
+            I_sigma[0] = a;
+            I_sigma[1] = sqrt(b > 0.0 ? b : 0.0);
+        }
+    }
+}
+
 __global__ void __launch_bounds__(256) current_sum_kernel(const double* __restrict__ T,
                                                           const double* __restrict__ sig,
                                                           const double* __restrict__ w, int nE,
-                                                          double* __restrict__ out) {
+                                                          double* __restrict__ reduce,
+                                                          double* __restrict__ I_sigma) {
     __shared__ double red[256];
     double a = 0.0, b = 0.0;
     for (int k = threadIdx.x; k < nE; k += 256) {
         a += w[k] * T[k];
         b += w[k] * w[k] * sig[k] * sig[k];
     }
-    a = block_reduce256(a, red);
-    b = block_reduce256(b, red);
-    if (threadIdx.x == 0) {
-        out[0] = a;
-        out[1] = b;
-    }
+    store_current(a, b, red, reduce, I_sigma);
 }
 
-__global__ void mc_current_kernel(const int64_t* __restrict__ tallies,
-                                  const double* __restrict__ lead, int nE, uint32_t inject_lead,
-                                  double* __restrict__ T, double* __restrict__ sig) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nE) return;
-    const int64_t* t = tallies + (size_t)k * MCNEGF_TALLY_N;
-    const double walkers =
-        (double)(t[MCNEGF_TALLY_EXIT_L] + t[MCNEGF_TALLY_EXIT_R] + t[MCNEGF_TALLY_TRUNC]);
-    const double hits = (double)(inject_lead == 0 ? t[MCNEGF_TALLY_EXIT_R] : t[MCNEGF_TALLY_EXIT_L]);
-    const double c = lead[(size_t)k * MCNEGF_LEAD_NTERMS +
-                          (inject_lead == 0 ? MCNEGF_LEAD_CL : MCNEGF_LEAD_CR)];
-    if (walkers <= 0.0) {
-        T[k] = 0.0;
-        sig[k] = 0.0;
-        return;
+// T_k and sigma_k of the tallies and their weighted sums.  One workgroup: the energies are few
+// and what a call costs here is launches (three of them, 18 us between events, before).
+__global__ void __launch_bounds__(256) mc_current_kernel(const int64_t* __restrict__ tallies,
+                                                         const double* __restrict__ lead,
+                                                         const double* __restrict__ w, int nE,
+                                                         uint32_t inject_lead,
+                                                         double* __restrict__ T,
+                                                         double* __restrict__ sig,
+                                                         double* __restrict__ reduce,
+                                                         double* __restrict__ I_sigma) {
+    __shared__ double red[256];
+    double a = 0.0, b = 0.0;
+#pragma unroll 4
+    for (int k = threadIdx.x; k < nE; k += 256) {
+        const int64_t* t = tallies + (size_t)k * MCNEGF_TALLY_N;
+        const double walkers =
+            (double)(t[MCNEGF_TALLY_EXIT_L] + t[MCNEGF_TALLY_EXIT_R] + t[MCNEGF_TALLY_TRUNC]);
+        const double hits =
+            (double)(inject_lead == 0 ? t[MCNEGF_TALLY_EXIT_R] : t[MCNEGF_TALLY_EXIT_L]);
+        const double c = lead[(size_t)k * MCNEGF_LEAD_NTERMS +
+                              (inject_lead == 0 ? MCNEGF_LEAD_CL : MCNEGF_LEAD_CR)];
+        const double p = walkers > 0.0 ? hits / walkers : 0.0;
+        const double Tk = walkers > 0.0 ? c * p : 0.0;
+        const double sk = walkers > 1.0 ? c * sqrt(p * (1.0 - p) / (walkers - 1.0)) : 0.0;
+        T[k] = Tk;
+        sig[k] = sk;
+        a += w[k] * Tk;
+        b += w[k] * w[k] * sk * sk;
     }
-    const double p = hits / walkers;
-    T[k] = c * p;
-    sig[k] = walkers > 1.0 ? c * sqrt(p * (1.0 - p) / (walkers - 1.0)) : 0.0;
+    store_current(a, b, red, reduce, I_sigma);
 }
 
 hipError_t launch_mc_current(const mcnegf_kernel& k, uint32_t inject_lead, const int64_t* tallies,
-                             const double* weights, double* T, double* sigmaT, hipStream_t s) {
+                             const double* weights, double* T, double* sigmaT, double* I_sigma,
+                             hipStream_t s) {
     {
         MCNEGF_TIMED("mc_current_kernel", s);
-        hipLaunchKernelGGL(mc_current_kernel, dim3((k.nE + 255) / 256), dim3(256), 0, s, tallies,
-                           k.lead, k.nE, inject_lead, T, sigmaT);
-    }
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    {
-        MCNEGF_TIMED("current_sum_kernel", s);
-        hipLaunchKernelGGL(current_sum_kernel, dim3(1), dim3(256), 0, s, T, sigmaT, weights, k.nE,
-                           k.reduce);
+        hipLaunchKernelGGL(mc_current_kernel, dim3(1), dim3(256), 0, s, tallies, k.lead, weights,
+                           k.nE, inject_lead, T, sigmaT, k.reduce, I_sigma);
     }
     return hipGetLastError();
 }
@@ -181,7 +197,7 @@ hipError_t launch_weighted_current(const mcnegf_kernel& k, uint32_t inject_lead,
     {
         MCNEGF_TIMED("current_sum_kernel", s);
         hipLaunchKernelGGL(current_sum_kernel, dim3(1), dim3(256), 0, s, T, sigmaT, weights, k.nE,
-                           k.reduce);
+                           k.reduce, nullptr);
     }
     return hipGetLastError();
 }
@@ -236,7 +252,7 @@ hipError_t launch_interp_current(const mcnegf_kernel& k, const double* fine, uin
     {
         MCNEGF_TIMED("current_sum_kernel", s);
         hipLaunchKernelGGL(current_sum_kernel, dim3(1), dim3(256), 0, s, T, sigmaT, weights,
-                           (int)nF, k.reduce);
+                           (int)nF, k.reduce, nullptr);
     }
     return hipGetLastError();
 }
@@ -1021,7 +1037,8 @@ static hipError_t factorize(CholArgs a, int cus, hipStream_t s) {
 }
 
 hipError_t launch_direct_current(const mcnegf_kernel& k, uint32_t inject_lead,
-                                 const double* weights, double* T, double* sigmaT, hipStream_t s) {
+                                 const double* weights, double* T, double* sigmaT,
+                                 double* I_sigma, hipStream_t s) {
     const int N = k.N;
     {
         MCNEGF_TIMED("direct_prep_kernel", s);
@@ -1057,7 +1074,7 @@ hipError_t launch_direct_current(const mcnegf_kernel& k, uint32_t inject_lead,
     {
         MCNEGF_TIMED("current_sum_kernel", s);
         hipLaunchKernelGGL(current_sum_kernel, dim3(1), dim3(256), 0, s, T, sigmaT, weights, k.nE,
-                           k.reduce);
+                           k.reduce, I_sigma);
     }
     return hipGetLastError();
 }

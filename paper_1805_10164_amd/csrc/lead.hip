@@ -32,9 +32,15 @@ __global__ void __launch_bounds__(256) lead_sigma_kernel(const double* __restric
                                                          int W, double t, int lead_model,
                                                          double gamma_l, double delta,
                                                          double2* __restrict__ sigma,
-                                                         double* __restrict__ gam) {
+                                                         double* __restrict__ gam,
+                                                         uint32_t* __restrict__ status,
+                                                         uint32_t* __restrict__ counters) {
     const int e = blockIdx.x;
     const int tid = threadIdx.x;
+    if (e == 0) {  // the first kernel of a build, so no other has set a flag yet
+        if (tid == 0) status[0] = 0u;
+        if (tid < 64) counters[tid] = 0u;
+    }
     __shared__ double2 s_mode[kMaxW];
     __shared__ double chi[kMaxW][kMaxW];
     const double E = energies[e];
@@ -72,27 +78,13 @@ __global__ void __launch_bounds__(256) lead_sigma_kernel(const double* __restric
     }
 }
 
-__global__ void clear_status_kernel(uint32_t* status, uint32_t* counters) {
-    const int tid = threadIdx.x;
-    if (tid == 0) status[0] = 0u;
-    if (tid < 64) counters[tid] = 0u;
-}
-
-hipError_t launch_clear_status(uint32_t* status, uint32_t* counters, hipStream_t s) {
-    {
-        MCNEGF_TIMED("clear_status_kernel", s);
-        hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(64), 0, s, status, counters);
-    }
-    return hipGetLastError();
-}
-
 hipError_t launch_lead_sigma(const mcnegf_kernel& k, double gamma_l, double delta,
                              hipStream_t s) {
     {
         MCNEGF_TIMED("lead_sigma_kernel", s);
         hipLaunchKernelGGL(lead_sigma_kernel, dim3(k.nE), dim3(256), 0, s, k.energies, k.W, k.t,
                            k.lead_model, gamma_l, delta, reinterpret_cast<double2*>(k.sigma),
-                           k.gam_lead);
+                           k.gam_lead, k.status, k.counters);
     }
     return hipGetLastError();
 }

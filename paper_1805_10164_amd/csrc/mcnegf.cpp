@@ -221,7 +221,6 @@ int32_t mc_negf_build_kernel(const mcnegf_system* sys, const double* d_onsite,
     k.ws_bytes = ws_bytes;
 
     hipError_t err;
-    if ((err = launch_clear_status(k.status, k.counters, stream)) != hipSuccess) return hip_fail(err);
     if ((err = launch_lead_sigma(k, sys->gamma_l, sys->delta_lead, stream)) != hipSuccess)
         return hip_fail(err);
     if ((err = (sys->flags & MCNEGF_BUILD_FP32_SWEEPS) ? launch_rgf_fp32(k, d_onsite, stream)
@@ -283,12 +282,12 @@ int32_t mc_negf_current(const mcnegf_kernel* k, int32_t mode, uint32_t inject_le
     if (mode == 0 || mode == 2) {
         if (!d_tallies || !k->alias) return MCNEGF_EINVAL;  // tallies need a walked kernel
         err = mode == 0 ? launch_mc_current(*k, inject_lead, d_tallies, d_weights, d_T, d_sigmaT,
-                                            stream)
+                                            nullptr, stream)
                         : launch_sampled_current(*k, inject_lead, d_tallies, d_weights, d_T,
                                                  d_sigmaT, stream);
     } else if (mode == 1) {
         if (!k->direct || !k->direct_vec) return MCNEGF_EINVAL;
-        err = launch_direct_current(*k, inject_lead, d_weights, d_T, d_sigmaT, stream);
+        err = launch_direct_current(*k, inject_lead, d_weights, d_T, d_sigmaT, nullptr, stream);
     } else {
         return MCNEGF_EINVAL;
     }
@@ -337,7 +336,7 @@ int32_t mc_negf_grad(const mcnegf_kernel* k, uint32_t inject_lead, const double*
     const int chunk = lo;
     GradBuffers gb;
     grad_layout(*k, chunk, d_gws, &gb);
-    hipError_t err = launch_direct_current(*k, inject_lead, d_weights, gb.T, gb.sig, stream);
+    hipError_t err = launch_direct_current(*k, inject_lead, d_weights, gb.T, gb.sig, nullptr, stream);
     if (err != hipSuccess) return hip_fail(err);
     if ((err = launch_grad(*k, gb, inject_lead, d_weights, d_dI_dV, d_dI_dgamma, chunk, stream)) !=
         hipSuccess)
@@ -532,17 +531,18 @@ int32_t mc_negf_current_async(const mcnegf_kernel* k, int32_t mode, uint32_t inj
     if (mode == 0 || mode == 2) {
         if (!d_tallies || !k->alias) return MCNEGF_EINVAL;
         err = mode == 0 ? launch_mc_current(*k, inject_lead, d_tallies, d_weights, d_T, d_sigmaT,
-                                            stream)
+                                            d_I_sigma, stream)
                         : launch_sampled_current(*k, inject_lead, d_tallies, d_weights, d_T,
                                                  d_sigmaT, stream);
     } else if (mode == 1) {
         if (!k->direct || !k->direct_vec) return MCNEGF_EINVAL;
-        err = launch_direct_current(*k, inject_lead, d_weights, d_T, d_sigmaT, stream);
+        err = launch_direct_current(*k, inject_lead, d_weights, d_T, d_sigmaT, d_I_sigma, stream);
     } else {
         return MCNEGF_EINVAL;
     }
     if (err != hipSuccess) return hip_fail(err);
-    if ((err = launch_current_out(*k, d_I_sigma, stream)) != hipSuccess) return hip_fail(err);
+    if (mode == 2 && (err = launch_current_out(*k, d_I_sigma, stream)) != hipSuccess)
+        return hip_fail(err);
     return MCNEGF_OK;
 }
 
