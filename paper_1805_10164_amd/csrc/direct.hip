@@ -420,11 +420,11 @@ __device__ inline dmfma4 aorig4(const CholArgs& a, const double* Pe, const doubl
             const double4 p = *reinterpret_cast<const double4*>(Pe + (size_t)si * a.ld + j);
             const dmfma4 pv = dmfma4{p.x, p.y, p.z, p.w};
             const double ui = ve[si];
+            // beyond N the other vectors of this energy are read and not used; with fewer than
+            // four sites those end before the padded columns do
+            const double* uj = ve + min(j, 4 * N - 4);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double uj = ve[j + r];  // beyond N: the next vector's, not used
-                out[r] = j + r < N ? -ui * uj * pv[r] : 0.0;
-            }
+            for (int r = 0; r < 4; ++r) out[r] = j + r < N ? -ui * uj[r] * pv[r] : 0.0;
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) out[r] = j + r == si ? 1.0 : out[r];
