@@ -348,8 +348,16 @@ __device__ inline void transpose_groups(double (&x)[4]) {
 // T = double: FP64 products throughout.  T = float (a build with FP32 block products): the
 // column state and the products are FP32 (the staged FP64 blocks are rounded as they are
 // read), |G|^2, the exit weights and the corners are formed from the FP32 state in FP64.
+// FP32 products form both halves, the upper one by a second sweep G_{k,l} = -t gL_k G_{k+1,l}
+// (k < l) up the wire, with the exit weights into L and G_{0,L-1} at its end: the two halves'
+// roundings are then independent of each other, as the sums over a probe's row and column expect.
+// A mirrored lower half has one rounding for both: the rms error of T_eff grew from 6.6e-8 to 8.4e-8
+// (W = 32, L = 50) and from 9.4e-8 to 1.5e-7 (W = 16, L = 120), the current's from 1.8e-8 to 3.3e-8,
+// that of |G|^2 after refinement by a quarter.  Nor is it faster: |G|^2, N = 3200, 16 energies
+// 0.47 ms at W = 16 (mirrored 0.61) and 0.64 ms at W = 32 (0.78).
 template <int W, int TC, int NW, bool STORE_G, typename T = double>
-__global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2* __restrict__ gR,
+__global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2* __restrict__ gL,
+                                                          const double2* __restrict__ gR,
                                                           const double2* __restrict__ Gd,
                                                           const double* __restrict__ gam_lead,
                                                           int L, double t, int64_t ldP,
@@ -363,9 +371,10 @@ __global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2*
     constexpr int BS = 2 * W * W;
     __shared__ double Ms_raw[2 * BS];
     lds_double* Ms = (lds_double*)Ms_raw;
+    constexpr bool BOTH = sizeof(T) == 4;  // both halves by their own sweeps
     // (first workgroup of an energy) Gamma and, double-buffered, the columns of slice 0 at the
     // current slice, [column][row]
-    constexpr int XN = STORE_G ? 1 : W * W;
+    constexpr int XN = STORE_G || BOTH ? 1 : W * W;
     __shared__ double Gs[XN];
     __shared__ double2 X[2][XN];
     const int N = W * L;
@@ -376,8 +385,9 @@ __global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2*
     const int cg0 = blockIdx.y * NW * 16 * TC;  // the workgroup's first column
     const int c0 = cg0 + (tid >> 6) * 16 * TC;  // this wavefront's first column
     const int kmin = cg0 / W;
-    const bool slice0 = !STORE_G && cg0 == 0;  // its first wavefront holds the columns of slice 0
+    const bool slice0 = !STORE_G && !BOTH && cg0 == 0;  // its first wavefront holds the columns of slice 0
     const size_t eb = (size_t)e * L * W * W;
+    const double2* gLe = gL + eb;
     const double2* gRe = gR + eb;
     const double2* Gde = Gd + eb;
     const double* gme = gam_lead + (size_t)e * W * W;
@@ -398,9 +408,9 @@ __global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2*
     typedef typename Mfma4<T>::type acc4;
     T vr[TC][RT][4], vi[TC][RT][4];
 
-    // one slice: v <- (-t) M v with M the block staged at buf, for the columns the sweep has
-    // passed (the others keep their diagonal block's column)
-    auto product = [&](const lds_double* buf, int k) {
+    // one slice: v <- (-t) M v with M the block staged at buf, for the columns whose slice the
+    // sweep has passed (the others keep their diagonal block's column)
+    auto product = [&](const lds_double* buf, int k, bool down = true) {
         acc4 cr[TC][RT], ci[TC][RT];
 #pragma unroll
         for (int tc = 0; tc < TC; ++tc)
@@ -436,13 +446,15 @@ __global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2*
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    vr[tc][rt][r] = k > l[tc] ? cr[tc][rt][r] : vr[tc][rt][r];
-                    vi[tc][rt][r] = k > l[tc] ? ci[tc][rt][r] : vi[tc][rt][r];
+                    const bool on = down ? k > l[tc] : k < l[tc];
+                    vr[tc][rt][r] = on ? cr[tc][rt][r] : vr[tc][rt][r];
+                    vi[tc][rt][r] = on ? ci[tc][rt][r] : vi[tc][rt][r];
                 }
     };
-    // entry (row, column) and, below the diagonal block, its transpose: four consecutive rows
-    // per lane, so that the four lane groups fill a 128-byte line of the transposed row
-    auto store = [&](int k) {
+    // entry (row, column) and, below the diagonal block (with one sweep), its transpose: four
+    // consecutive rows per lane, so that the four lane groups fill a 128-byte line of the transposed
+    // row
+    auto store = [&](int k, bool down = true) {
 #pragma unroll
         for (int tc = 0; tc < TC; ++tc)
 #pragma unroll
@@ -454,16 +466,16 @@ __global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2*
                     xi[r] = vi[tc][rt][r];
                     if (!STORE_G) xr[r] = xr[r] * xr[r] + xi[r] * xi[r];
                     const size_t row = k * W + 16 * rt + tile_row<T>(r, g);
-                    if (valid[tc] && k >= l[tc]) {
+                    if (valid[tc] && (down ? k >= l[tc] : k < l[tc])) {
                         if (STORE_G) Ge[row * ldG + col[tc]] = cmk(xr[r], xi[r]);
                         else Pe[row * ldP + col[tc]] = xr[r];
                     }
                 }
-                if (sizeof(T) == 8) {
+                if (!BOTH) {
                     transpose_groups(xr);
                     if (STORE_G) transpose_groups(xi);
                 }
-                if (valid[tc] && k > l[tc]) {
+                if (!BOTH && valid[tc] && k > l[tc]) {
                     const size_t c4 = k * W + 16 * rt + 4 * g;
                     if (STORE_G) {
 #pragma unroll
@@ -522,17 +534,20 @@ __global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2*
         return q;
     };
 
+    auto start = [&] {
 #pragma unroll
-    for (int tc = 0; tc < TC; ++tc)
+        for (int tc = 0; tc < TC; ++tc)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
+            for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double2 d =
-                    Gde[((size_t)l[tc] * W + 16 * rt + tile_row<T>(r, g)) * W + y0[tc]];
-                vr[tc][rt][r] = (T)d.x;
-                vi[tc][rt][r] = (T)d.y;
-            }
+                for (int r = 0; r < 4; ++r) {
+                    const double2 d =
+                        Gde[((size_t)l[tc] * W + 16 * rt + tile_row<T>(r, g)) * W + y0[tc]];
+                    vr[tc][rt][r] = (T)d.x;
+                    vi[tc][rt][r] = (T)d.y;
+                }
+    };
+    start();
     if (slice0)
         for (int i = tid; i < W * W; i += 64 * NW) Gs[i] = gme[i];
     StagedBlock<W, 64 * NW> st;  // block k + 1 at the top of slice k
@@ -558,27 +573,47 @@ __global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2*
                             cmk(vr[tc][rt][r], vi[tc][rt][r]);
         }
     }
-    if (STORE_G) return;
     if (slice0) {  // the whole workgroup
         __syncthreads();
         exit_left(L - 1);
     }
+    // the exit weights at the end of a sweep and, for the columns of the opposite end slice, the
+    // corner block; with one sweep the other corner block is its transpose
+    auto finish = [&](bool down) {
 #pragma unroll
-    for (int tc = 0; tc < TC; ++tc) {
-        const double q = quad(tc);
-        if (valid[tc] && g == 0) wR[(size_t)e * N + col[tc]] = q;
-        if (valid[tc] && l[tc] == 0) {
-            double2* cRL = corner + (size_t)e * 2 * W * W;
-            double2* cLR = cRL + W * W;  // its transpose
+        for (int tc = 0; tc < TC; ++tc) {
+            const double q = quad(tc);
+            if (valid[tc] && g == 0) (down ? wR : wL)[(size_t)e * N + col[tc]] = q;
+            if (valid[tc] && l[tc] == (down ? 0 : L - 1)) {
+                double2* c = corner + ((size_t)e * 2 + (down ? 0 : 1)) * W * W;
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
+                for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int y = 16 * rt + tile_row<T>(r, g);
-                    cRL[y * W + y0[tc]] = cmk(vr[tc][rt][r], vi[tc][rt][r]);
-                    cLR[y0[tc] * W + y] = cmk(vr[tc][rt][r], vi[tc][rt][r]);
-                }
+                    for (int r = 0; r < 4; ++r) {
+                        const int y = 16 * rt + tile_row<T>(r, g);
+                        c[y * W + y0[tc]] = cmk(vr[tc][rt][r], vi[tc][rt][r]);
+                        if (!BOTH) c[W * W + y0[tc] * W + y] = cmk(vr[tc][rt][r], vi[tc][rt][r]);
+                    }
+            }
         }
+    };
+    if (!STORE_G) finish(true);
+    if constexpr (BOTH) {
+        const int kmax = (min(cg0 + NW * 16 * TC, N) - 1) / W;
+        start();
+        __syncthreads();  // the downward sweep's reads are done
+        st.load(gLe + (size_t)kmax * W * W, tid);
+        st.write(Ms, tid);
+        st.load(gLe + (size_t)max(kmax - 1, 0) * W * W, tid);
+        for (int k = kmax; k >= 0; --k) {
+            __syncthreads();
+            const int b = (kmax - k) & 1;
+            st.write(Ms + (b ^ 1) * BS, tid);
+            st.load(gLe + (size_t)max(k - 2, 0) * W * W, tid);
+            product(Ms + b * BS, k, false);
+            store(k, false);
+        }
+        if (!STORE_G) finish(false);
     }
 }
 
@@ -589,6 +624,7 @@ static hipError_t launch_fullinv_mfma(const mcnegf_kernel& k, double2* Gc, int64
     {
         MCNEGF_TIMED(STORE_G ? "fullinv_store_g_kernel" : "fullinv_kernel", s);
         hipLaunchKernelGGL((fullinv_mfma_kernel<W, TC, NW, STORE_G, T>), grid, dim3(64 * NW), 0, s,
+                           reinterpret_cast<const double2*>(k.gL),
                            reinterpret_cast<const double2*>(k.gR),
                            reinterpret_cast<const double2*>(k.Gd), k.gam_lead, k.L, k.t, k.p_pitch,
                            k.P, k.wL, k.wR, reinterpret_cast<double2*>(k.corner), Gc, ldG);
