@@ -47,54 +47,95 @@ __device__ inline double block_sum256(double v, double* red) {
 
 // Tr Gamma X Gamma X^+ = sum_{q,c} (Gamma X)_qc conj((X Gamma)_qc) for the four end blocks X
 // (Gamma real symmetric), and Tr Gamma A of the two diagonal ones: W^2 entries of O(W) work, the
-// blocks in LDS.  Four workgroups per energy, one block each: O(W^3) instead of the O(W^4) of
-// the plain double sum (W = 32, 8 energies 1.81 -> 0.02 ms).
+// blocks in LDS (W = 32, 8 energies 1.81 -> 0.02 ms against the O(W^4) plain double sum).
+// Above W = 8 a workgroup per energy and block, four in y.  Up to W = 8 the W^2 entries are one
+// wavefront's, so the four wavefronts of a workgroup take the four blocks of an energy and sum by
+// lane exchanges: what the many energies of a narrow wire cost is workgroups and their barriers
+// (W = 1, 70000 energies: 0.50 ms with four workgroups of block sums per energy, 0.09 here).
+struct LeadEntry {
+    double tr, ga;  // (Gamma X)_qc conj((X Gamma)_qc) and Gamma_cq A_qc of the block
+};
+
+__device__ inline const double2* end_block(const double2* Gd, const double2* corner, int e, int W,
+                                           int L, int which) {  // LL, RL, LR, RR
+    const double2* G00 = Gd + (size_t)e * L * W * W;
+    const double2* cRL = corner + (size_t)e * 2 * W * W;
+    return which == 0 ? G00 : which == 1 ? cRL : which == 2 ? cRL + W * W
+                                                             : G00 + (size_t)(L - 1) * W * W;
+}
+
+// Entry (q, c) of the block X and Gamma gm, both of row pitch ld.
+__device__ inline void add_lead_entry(LeadEntry& s, const double2* X, const double* gm, int ld,
+                                      int W, int q, int c) {
+    double2 gx = cmk(0.0, 0.0), xg = cmk(0.0, 0.0);
+    for (int d = 0; d < W; ++d) {
+        gx = cadd(gx, cscale(X[d * ld + c], gm[q * ld + d]));
+        xg = cadd(xg, cscale(X[q * ld + d], gm[d * ld + c]));
+    }
+    s.tr = fma(gx.x, xg.x, fma(gx.y, xg.y, s.tr));
+    // A[q][c] = i (G[q][c] - conj(G[c][q])), real part
+    s.ga = fma(-gm[c * ld + q], X[q * ld + c].y + X[c * ld + q].y, s.ga);
+}
+
+__device__ inline void store_lead_terms(double* o, int which, double tr, double ga) {
+    const int slot[4] = {MCNEGF_LEAD_TLL, MCNEGF_LEAD_TRL, MCNEGF_LEAD_TLR, MCNEGF_LEAD_TRR};
+    o[slot[which]] = tr;
+    if (which == 0) o[MCNEGF_LEAD_TRGLA] = ga;
+    if (which == 3) o[MCNEGF_LEAD_TRGRA] = ga;
+}
+
 __global__ void __launch_bounds__(256) lead_terms_kernel(const double2* __restrict__ Gd,
                                                          const double2* __restrict__ corner,
                                                          const double* __restrict__ gam_lead,
                                                          int W, int L, double* __restrict__ lead) {
+    constexpr int LD = kMaxW + 1;
     __shared__ double red[256];
-    __shared__ double2 X[kMaxW][kMaxW + 1];
-    __shared__ double gm[kMaxW][kMaxW + 1];
-    const int e = blockIdx.x >> 2;
-    const int which = blockIdx.x & 3;  // LL, RL, LR, RR
+    __shared__ double2 X[kMaxW * LD];
+    __shared__ double gm[kMaxW * LD];
+    const int e = blockIdx.x, which = blockIdx.y;
     const int tid = threadIdx.x;
-    const double2* G00 = Gd + (size_t)e * L * W * W;
-    const double2* cRL = corner + (size_t)e * 2 * W * W;
-    const double2* src = which == 0 ? G00 : which == 1 ? cRL : which == 2 ? cRL + W * W
-                                                             : G00 + (size_t)(L - 1) * W * W;
+    const double2* src = end_block(Gd, corner, e, W, L, which);
     for (int i = tid; i < W * W; i += 256) {
-        X[i / W][i % W] = src[i];
-        gm[i / W][i % W] = gam_lead[(size_t)e * W * W + i];
+        X[i / W * LD + i % W] = src[i];
+        gm[i / W * LD + i % W] = gam_lead[(size_t)e * W * W + i];
     }
     __syncthreads();
-    double tr = 0.0, ga = 0.0;
-    for (int i = tid; i < W * W; i += 256) {
-        const int q = i / W, c = i % W;
-        double2 gx = cmk(0.0, 0.0), xg = cmk(0.0, 0.0);
-        for (int d = 0; d < W; ++d) {
-            gx = cadd(gx, cscale(X[d][c], gm[q][d]));
-            xg = cadd(xg, cscale(X[q][d], gm[d][c]));
-        }
-        tr = fma(gx.x, xg.x, fma(gx.y, xg.y, tr));
-        // A[q][c] = i (G[q][c] - conj(G[c][q])), real part
-        ga = fma(-gm[c][q], X[q][c].y + X[c][q].y, ga);
+    LeadEntry s = {0.0, 0.0};
+    for (int i = tid; i < W * W; i += 256) add_lead_entry(s, X, gm, LD, W, i / W, i % W);
+    s.tr = block_sum256(s.tr, red);
+    s.ga = block_sum256(s.ga, red);
+    if (tid == 0) store_lead_terms(lead + (size_t)e * MCNEGF_LEAD_NTERMS, which, s.tr, s.ga);
+}
+
+__global__ void __launch_bounds__(256) lead_terms_narrow_kernel(
+    const double2* __restrict__ Gd, const double2* __restrict__ corner,
+    const double* __restrict__ gam_lead, int W, int L, double* __restrict__ lead) {
+    __shared__ double2 X[4][64];
+    __shared__ double gm[4][64];
+    const int e = blockIdx.x, which = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const double2* src = end_block(Gd, corner, e, W, L, which);
+    if (lane < W * W) {
+        X[which][lane] = src[lane];
+        gm[which][lane] = gam_lead[(size_t)e * W * W + lane];
     }
-    tr = block_sum256(tr, red);
-    ga = block_sum256(ga, red);
-    if (tid == 0) {
-        double* o = lead + (size_t)e * MCNEGF_LEAD_NTERMS;
-        const int slot[4] = {MCNEGF_LEAD_TLL, MCNEGF_LEAD_TRL, MCNEGF_LEAD_TLR, MCNEGF_LEAD_TRR};
-        o[slot[which]] = tr;
-        if (which == 0) o[MCNEGF_LEAD_TRGLA] = ga;
-        if (which == 3) o[MCNEGF_LEAD_TRGRA] = ga;
+    __syncthreads();
+    LeadEntry s = {0.0, 0.0};
+    if (lane < W * W) add_lead_entry(s, X[which], gm[which], W, W, lane / W, lane % W);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        s.tr += __shfl_xor(s.tr, o, 64);
+        s.ga += __shfl_xor(s.ga, o, 64);
     }
+    if (lane == 0) store_lead_terms(lead + (size_t)e * MCNEGF_LEAD_NTERMS, which, s.tr, s.ga);
 }
 
 hipError_t launch_lead_terms(const mcnegf_kernel& k, hipStream_t s) {
     {
         MCNEGF_TIMED("lead_terms_kernel", s);
-        hipLaunchKernelGGL(lead_terms_kernel, dim3(4 * k.nE), dim3(256), 0, s,
+        const bool narrow = k.W <= 8;
+        hipLaunchKernelGGL(narrow ? lead_terms_narrow_kernel : lead_terms_kernel,
+                           dim3(k.nE, narrow ? 1 : 4), dim3(256), 0, s,
                            reinterpret_cast<const double2*>(k.Gd),
                            reinterpret_cast<const double2*>(k.corner), k.gam_lead, k.W, k.L, k.lead);
     }
