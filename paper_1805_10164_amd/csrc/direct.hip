@@ -63,45 +63,79 @@ __global__ void __launch_bounds__(256) current_sum_kernel(const double* __restri
     store_current(a, b, red, reduce, I_sigma);
 }
 
-// T_k and sigma_k of the tallies and their weighted sums.  One workgroup: the energies are few
-// and what a call costs here is launches (three of them, 18 us between events, before).
-__global__ void __launch_bounds__(256) mc_current_kernel(const int64_t* __restrict__ tallies,
-                                                         const double* __restrict__ lead,
-                                                         const double* __restrict__ w, int nE,
-                                                         uint32_t inject_lead,
-                                                         double* __restrict__ T,
-                                                         double* __restrict__ sig,
+struct McCurrentArgs {
+    const int64_t* tallies;
+    const double* lead;
+    int nE;
+    uint32_t inject_lead;
+    double* T;
+    double* sig;
+};
+
+// T_k and sigma_k of energy k's tallies, stored and returned.
+__device__ inline double2 mc_current_entry(const McCurrentArgs& m, int k) {
+    const int64_t* t = m.tallies + (size_t)k * MCNEGF_TALLY_N;
+    const double walkers =
+        (double)(t[MCNEGF_TALLY_EXIT_L] + t[MCNEGF_TALLY_EXIT_R] + t[MCNEGF_TALLY_TRUNC]);
+    const double hits =
+        (double)(m.inject_lead == 0 ? t[MCNEGF_TALLY_EXIT_R] : t[MCNEGF_TALLY_EXIT_L]);
+    const double c = m.lead[(size_t)k * MCNEGF_LEAD_NTERMS +
+                            (m.inject_lead == 0 ? MCNEGF_LEAD_CL : MCNEGF_LEAD_CR)];
+    const double p = walkers > 0.0 ? hits / walkers : 0.0;
+    const double Tk = walkers > 0.0 ? c * p : 0.0;
+    const double sk = walkers > 1.0 ? c * sqrt(p * (1.0 - p) / (walkers - 1.0)) : 0.0;
+    m.T[k] = Tk;
+    m.sig[k] = sk;
+    return cmk(Tk, sk);
+}
+
+// The entries and their weighted sums in one workgroup: with few energies what a call costs is
+// launches (three of them, 18 us between events, before).
+__global__ void __launch_bounds__(256) mc_current_kernel(McCurrentArgs m,
+                                                         const double* __restrict__ w,
                                                          double* __restrict__ reduce,
                                                          double* __restrict__ I_sigma) {
     __shared__ double red[256];
     double a = 0.0, b = 0.0;
 #pragma unroll 4
-    for (int k = threadIdx.x; k < nE; k += 256) {
-        const int64_t* t = tallies + (size_t)k * MCNEGF_TALLY_N;
-        const double walkers =
-            (double)(t[MCNEGF_TALLY_EXIT_L] + t[MCNEGF_TALLY_EXIT_R] + t[MCNEGF_TALLY_TRUNC]);
-        const double hits =
-            (double)(inject_lead == 0 ? t[MCNEGF_TALLY_EXIT_R] : t[MCNEGF_TALLY_EXIT_L]);
-        const double c = lead[(size_t)k * MCNEGF_LEAD_NTERMS +
-                              (inject_lead == 0 ? MCNEGF_LEAD_CL : MCNEGF_LEAD_CR)];
-        const double p = walkers > 0.0 ? hits / walkers : 0.0;
-        const double Tk = walkers > 0.0 ? c * p : 0.0;
-        const double sk = walkers > 1.0 ? c * sqrt(p * (1.0 - p) / (walkers - 1.0)) : 0.0;
-        T[k] = Tk;
-        sig[k] = sk;
-        a += w[k] * Tk;
-        b += w[k] * w[k] * sk * sk;
+    for (int k = threadIdx.x; k < m.nE; k += 256) {
+        const double2 Ts = mc_current_entry(m, k);
+        a += w[k] * Ts.x;
+        b += w[k] * w[k] * Ts.y * Ts.y;
     }
     store_current(a, b, red, reduce, I_sigma);
 }
 
+__global__ void __launch_bounds__(256) mc_entries_kernel(McCurrentArgs m) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < m.nE) mc_current_entry(m, k);
+}
+
+// One workgroup for entries and sums up to 8192 energies (4096: 13.6 us between events, 16.5 as
+// launches of their own; 16384: 26 both ways), above that the entries over the whole chip, then
+// the sums (70000: 154 us in one workgroup, 81 here).  Both add in the same order.
+constexpr int kOneGroupEnergies = 8192;
+
 hipError_t launch_mc_current(const mcnegf_kernel& k, uint32_t inject_lead, const int64_t* tallies,
                              const double* weights, double* T, double* sigmaT, double* I_sigma,
                              hipStream_t s) {
+    const McCurrentArgs m = {tallies, k.lead, k.nE, inject_lead, T, sigmaT};
+    if (k.nE <= kOneGroupEnergies) {
+        MCNEGF_TIMED("mc_current_kernel", s);
+        hipLaunchKernelGGL(mc_current_kernel, dim3(1), dim3(256), 0, s, m, weights, k.reduce,
+                           I_sigma);
+        return hipGetLastError();
+    }
     {
         MCNEGF_TIMED("mc_current_kernel", s);
-        hipLaunchKernelGGL(mc_current_kernel, dim3(1), dim3(256), 0, s, tallies, k.lead, weights,
-                           k.nE, inject_lead, T, sigmaT, k.reduce, I_sigma);
+        hipLaunchKernelGGL(mc_entries_kernel, dim3((k.nE + 255) / 256), dim3(256), 0, s, m);
+    }
+    hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    {
+        MCNEGF_TIMED("current_sum_kernel", s);
+        hipLaunchKernelGGL(current_sum_kernel, dim3(1), dim3(256), 0, s, T, sigmaT, weights, k.nE,
+                           k.reduce, I_sigma);
     }
     return hipGetLastError();
 }
