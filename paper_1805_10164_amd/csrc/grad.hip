@@ -44,8 +44,9 @@ __device__ inline double readlane_dbl(double v, int lane) {
 
 // L^T xt = y and L^T lt = z with L the Cholesky factor of the bordered scaled probe system
 // (lower part, columns of each 16-block stored permuted, logical row and column i being site
-// perm16(i)) and y, z its bordered rows Np and Np + 1; then x = s xt and lambda = s lt (s_j = M_jj^{-1/2}, vector slot 3).  One workgroup
-// of 1024 threads per energy, right-looking over block rows of 64 from the last one down:
+// perm16(i)) and y, z its bordered rows Np and Np + 1; then x = s xt and lambda = s lt
+// (s_j = M_jj^{-1/2}, vector slot 3).  One workgroup of 1024 threads per energy, right-looking over
+// block rows of 64 from the last one down:
 //   solve  L_II^T x_I = r_I       (diagonal block staged in LDS, one wavefront, lane per row)
 //   update r_j -= sum_{i in I} L_ij x_i   for every j < 64 I
 // Thread tid owns the stored positions p = tid + 1024 q of r (in registers), so the update
@@ -182,8 +183,8 @@ struct AdjointArgs {
 };
 
 // The lead columns of one energy, on one wavefront: right-hand side c < W is
-// column sq + c of Q (d = v), c = W + b is column sp + b of R (d = u), one lane each; y goes to Y and q replaces it.  A chain of 2 L slices: it shares its launch
-// with the dense columns.
+// column sq + c of Q (d = v), c = W + b is column sp + b of R (d = u), one lane each; y goes to Y
+// and q replaces it.  A chain of 2 L slices: it shares its launch with the dense columns.
 template <int W>
 __device__ inline void adjoint_lead_columns(const AdjointArgs& a, int e, lds_double* Ms) {
     constexpr int BS = 2 * W * W;
@@ -247,13 +248,19 @@ __device__ inline double other_half(double v) {  // of lane + 32, in lanes 0 .. 
     return __hiloint2double(hi[1], lo[1]);
 }
 
-// Dense columns on the VALU: a wavefront owns 32 columns, lanes 0 .. 31 eliminate h^v, lanes
-// 32 .. 63 h^u, and the blocks gL_k are broadcast from LDS to both (double-buffered, one slice
-// ahead).  Per column
+// Dense columns on the VALU (up to W = 15): a wavefront owns 32 columns, lanes 0 .. 31 eliminate
+// h^v, lanes 32 .. 63 h^u, and the blocks gL_k are broadcast from LDS to both (double-buffered, one
+// slice ahead).  Per column
 //   kd = sum_k (w^u_k)^T y^v_k,  kg = sum_a G_ac^2 u_a x_a,  pv = sum_a |G_ac|^2 v_a,  pu (u).
 // The first workgroup of an energy takes the lead columns instead.
+// Above W = 12 the registers are held to two wavefronts per SIMD, no fewer and no more, and the
+// rows of G and of the final sums are taken four at a time (all at once, they cost a wavefront at
+// W = 15; held to three, the LDS operands come too late): W = 15, N = 2400, 16 energies 4.46 ->
+// 2.46 ms, W = 14 2.48 -> 2.38.
 template <int W>
-__global__ void __launch_bounds__(64) adjoint_solve_kernel(AdjointArgs a) {
+__global__ void __launch_bounds__(64)
+    __attribute__((amdgpu_waves_per_eu(W > 12 ? 2 : 1, W > 12 ? 2 : 8)))
+    adjoint_solve_kernel(AdjointArgs a) {
     constexpr int BS = 2 * W * W;  // doubles per buffer
     __shared__ double Ms_raw[2 * BS];
     lds_double* Ms = (lds_double*)Ms_raw;
@@ -293,11 +300,16 @@ __global__ void __launch_bounds__(64) adjoint_solve_kernel(AdjointArgs a) {
             const double p = cabs2(g);
             pv = fma(p, va, pv);
             pu = fma(p, ua, pu);
+            if (W > 12 && r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
+        if (W > 12) __builtin_amdgcn_sched_barrier(0);
         conj_block_matvec<W>(y, w, Ms + (k & 1) * BS);
+        if (W > 12) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < W; ++r)
+        for (int r = 0; r < W; ++r) {
             cfma(kd, cmk(other_half(w[r].x), other_half(w[r].y)), y[r]);
+            if (W > 12 && r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
     }
     if (!half_u && c < N) {
         a.part_k[((size_t)e * 2 + 0) * N + c] = kd;
@@ -307,27 +319,61 @@ __global__ void __launch_bounds__(64) adjoint_solve_kernel(AdjointArgs a) {
     }
 }
 
-// Dense columns at W = 16 and 32 on the FP64 matrix cores: a wavefront owns TC tiles of 16
+// Dense columns from W = 16 on, on the FP64 matrix cores: a wavefront owns TC tiles of 16
 // columns and both eliminations of each; lane (n, g) holds the rows 16 rt + 4 r + g of column n,
 // which is the accumulator layout of one product and the B operand of the next, so w and y
 // never leave registers; the staged block is the A operand (NW wavefronts share it).  G is read
 // one slice ahead, under the products (64 clocks each, 4 (W / 4) (W / 16) per complex tile).
 // N = 3200, 128 energies: 22.9 -> 7.6 ms (44 TFLOP/s; G read at 2.8 TB/s); W = 32, N = 4160,
 // 16 energies 25.5 -> 4.1 ms.
+// Widths between 16 and 32 are padded to 32 rows of zeros (a padded row reads a row of its block
+// and multiplies it by a zero rate; steps of four padded columns are left out).  On the VALU both
+// eliminations of a column take 8 W registers at once, which from W = 17 on leaves one wavefront
+// per SIMD: N = 2400, 16 energies, W = 17 5.04 -> 1.74 ms, W = 24 6.39 -> 1.45 ms, W = 31 11.3 ->
+// 1.84 ms (with a full solve per column 2.7, 4.4 and 7.3 ms).
 typedef double dmfma4 __attribute__((ext_vector_type(4)));
+
+// Rows a block of width W takes on the matrix cores.
+constexpr int padded(int W) { return (W + 15) / 16 * 16; }
+// Padded row y: whether the block has it, and a row of the block to read in its place.
+template <int W>
+__device__ inline bool has_row(int y) {
+    return W == padded(W) || y < W;
+}
+template <int W>
+__device__ inline int row_in_block(int y) {
+    return W == padded(W) ? y : min(y, W - 1);
+}
+
+// The block src into the LDS buffer dst of padded rows; the padding stays zero.
+template <int W, int NT>
+__device__ inline void stage_padded(lds_double* dst, const double2* __restrict__ src, int tid) {
+    if constexpr (W == padded(W)) {
+        stage_block<W, NT>(dst, src, tid);
+    } else {
+#pragma unroll
+        for (int i = tid; i < W * W; i += NT) {
+            const double2 v = src[i];
+            const int at = 2 * (i / W * padded(W) + i % W);
+            dst[at] = v.x;
+            dst[at + 1] = v.y;
+        }
+    }
+}
 
 // (yr, yi)[i] = conj(M) (wr, wi)[i] for V vectors, M staged in LDS.
 template <int W, int V>
-__device__ inline void conj_product(dmfma4 (&yr)[V][W / 16], dmfma4 (&yi)[V][W / 16],
-                                    const dmfma4 (&wr)[V][W / 16], const dmfma4 (&wi)[V][W / 16],
-                                    const lds_double* M, int n, int g) {
+__device__ inline void conj_product(dmfma4 (&yr)[V][padded(W) / 16], dmfma4 (&yi)[V][padded(W) / 16],
+                                    const dmfma4 (&wr)[V][padded(W) / 16],
+                                    const dmfma4 (&wi)[V][padded(W) / 16], const lds_double* M,
+                                    int n, int g) {
 #pragma unroll
-    for (int rt = 0; rt < W / 16; ++rt) {
+    for (int rt = 0; rt < padded(W) / 16; ++rt) {
 #pragma unroll
         for (int i = 0; i < V; ++i) yr[i][rt] = yi[i][rt] = dmfma4{0, 0, 0, 0};
 #pragma unroll
-        for (int s = 0; s < W / 4; ++s) {
-            const int at = 2 * ((16 * rt + n) * W + 4 * s + g);
+        for (int s = 0; s < (W + 3) / 4; ++s) {
+            const int at = 2 * ((16 * rt + n) * padded(W) + 4 * s + g);
             const double ar = M[at], ai = M[at + 1];  // conj: ar - i ai
 #pragma unroll
             for (int i = 0; i < V; ++i) {
@@ -348,14 +394,17 @@ __device__ inline void conj_product(dmfma4 (&yr)[V][W / 16], dmfma4 (&yi)[V][W /
 // The lead columns of one energy (see adjoint_lead_columns), 16 per wavefront.
 template <int W>
 __device__ inline void adjoint_lead_mfma(const AdjointArgs& a, int e, lds_double* Ms) {
-    constexpr int RT = W / 16, BS = 2 * W * W, NT = 8 * W;  // 2 W columns: W / 8 wavefronts
+    constexpr int P = padded(W), RT = P / 16, BS = 2 * P * P;
+    constexpr int NT = 8 * P;  // 2 W columns, 16 per wavefront
     const int N = W * a.L;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
     const int sp = a.inject_lead == 0 ? 0 : N - W;
     const int sq = a.inject_lead == 0 ? N - W : 0;
-    const int c = 16 * (tid >> 6) + n;
+    const int lc = 16 * (tid >> 6) + n;
+    const bool on = W == P || lc < 2 * W;
+    const int c = on ? lc : 0;
     const bool isq = c < W;
     const int col = isq ? sq + c : sp + c - W;  // column of G
     const int yc = isq ? sq + c : N + c - W;    // column of Y
@@ -367,17 +416,18 @@ __device__ inline void adjoint_lead_mfma(const AdjointArgs& a, int e, lds_double
     dmfma4 yr[1][RT], yi[1][RT], wr[1][RT], wi[1][RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) yr[0][rt] = yi[0][rt] = dmfma4{0, 0, 0, 0};
-    stage_block<W, NT>(Ms, gLe, tid);
+    stage_padded<W, NT>(Ms, gLe, tid);
     for (int k = 0; k < a.L; ++k) {
         __syncthreads();
         if (k + 1 < a.L)
-            stage_block<W, NT>(Ms + ((k + 1) & 1) * BS, gLe + (size_t)(k + 1) * W * W, tid);
+            stage_padded<W, NT>(Ms + ((k + 1) & 1) * BS, gLe + (size_t)(k + 1) * W * W, tid);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int row = k * W + 16 * rt + 4 * r + g;
-                const double d = a.gamma[row] * de[row];
+                const int y = 16 * rt + 4 * r + g;
+                const int row = k * W + row_in_block<W>(y);
+                const double d = has_row<W>(y) ? a.gamma[row] * de[row] : 0.0;
                 const double2 v = Ge[(size_t)row * a.ld + col];
                 wr[0][rt][r] = fma(d, v.x, -a.t * yr[0][rt][r]);
                 wi[0][rt][r] = fma(d, v.y, -a.t * yi[0][rt][r]);
@@ -386,39 +436,47 @@ __device__ inline void adjoint_lead_mfma(const AdjointArgs& a, int e, lds_double
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                Ye[(size_t)(k * W + 16 * rt + 4 * r + g) * a.ldY + yc] =
-                    cmk(yr[0][rt][r], yi[0][rt][r]);
+            for (int r = 0; r < 4; ++r) {
+                const int y = 16 * rt + 4 * r + g;
+                if (on && has_row<W>(y))
+                    Ye[(size_t)(k * W + y) * a.ldY + yc] = cmk(yr[0][rt][r], yi[0][rt][r]);
+            }
     }
     __syncthreads();
-    if (a.L > 1) stage_block<W, NT>(Ms, gLe + (size_t)(a.L - 2) * W * W, tid);
+    if (a.L > 1) stage_padded<W, NT>(Ms, gLe + (size_t)(a.L - 2) * W * W, tid);
     for (int k = a.L - 2; k >= 0; --k) {
         const int j = a.L - 2 - k;
         __syncthreads();
         if (k > 0)
-            stage_block<W, NT>(Ms + ((j + 1) & 1) * BS, gLe + (size_t)(k - 1) * W * W, tid);
+            stage_padded<W, NT>(Ms + ((j + 1) & 1) * BS, gLe + (size_t)(k - 1) * W * W, tid);
         conj_product<W, 1>(wr, wi, yr, yi, Ms + (j & 1) * BS, n, g);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                double2* at = Ye + (size_t)(k * W + 16 * rt + 4 * r + g) * a.ldY + yc;
-                yr[0][rt][r] = fma(-a.t, wr[0][rt][r], at->x);
-                yi[0][rt][r] = fma(-a.t, wi[0][rt][r], at->y);
-                *at = cmk(yr[0][rt][r], yi[0][rt][r]);
+                const int y = 16 * rt + 4 * r + g;
+                double2* at = Ye + (size_t)(k * W + row_in_block<W>(y)) * a.ldY + yc;
+                const double2 v = *at;
+                yr[0][rt][r] = has_row<W>(y) ? fma(-a.t, wr[0][rt][r], v.x) : 0.0;
+                yi[0][rt][r] = has_row<W>(y) ? fma(-a.t, wi[0][rt][r], v.y) : 0.0;
+                if (on && has_row<W>(y)) *at = cmk(yr[0][rt][r], yi[0][rt][r]);
             }
     }
 }
 
-// One workgroup of W / 8 wavefronts: the lead columns (first workgroup of an energy), else
-// 16 TC dense columns per wavefront, TC = 32 / W.
+// One workgroup of P / 8 wavefronts (P the padded width): the lead columns (first workgroup of an
+// energy), else 16 TC dense columns per wavefront, TC = 32 / P.
 template <int W>
-__global__ void __launch_bounds__(8 * W, 2) adjoint_mfma_kernel(AdjointArgs a) {
-    constexpr int TC = 32 / W, NW = W / 8;
-    constexpr int RT = W / 16, BS = 2 * W * W, NT = 64 * NW;
+__global__ void __launch_bounds__(8 * padded(W), 2) adjoint_mfma_kernel(AdjointArgs a) {
+    constexpr int P = padded(W), TC = 32 / P, NW = P / 8;
+    constexpr int RT = P / 16, BS = 2 * P * P, NT = 64 * NW;
     __shared__ double Ms_raw[2 * BS];
     lds_double* Ms = (lds_double*)Ms_raw;
     const int e = blockIdx.y;
+    if constexpr (W != P) {
+        for (int i = threadIdx.x; i < 2 * BS; i += NT) Ms[i] = 0.0;
+        __syncthreads();
+    }
     if (blockIdx.x == 0) {
         adjoint_lead_mfma<W>(a, e, Ms);
         return;
@@ -453,8 +511,9 @@ __global__ void __launch_bounds__(8 * W, 2) adjoint_mfma_kernel(AdjointArgs a) {
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int row = k * W + 16 * rt + 4 * r + g;
-                gam[rt][r] = a.gamma[row];
+                const int y = 16 * rt + 4 * r + g;
+                const int row = k * W + row_in_block<W>(y);
+                gam[rt][r] = has_row<W>(y) ? a.gamma[row] : 0.0;
                 xk[rt][r] = xe[row];
                 lk[rt][r] = le[row];
 #pragma unroll
@@ -466,11 +525,11 @@ __global__ void __launch_bounds__(8 * W, 2) adjoint_mfma_kernel(AdjointArgs a) {
             }
     };
     read(0);
-    stage_block<W, NT>(Ms, gLe, tid);
+    stage_padded<W, NT>(Ms, gLe, tid);
     for (int k = 0; k < a.L; ++k) {
         __syncthreads();
         if (k + 1 < a.L)
-            stage_block<W, NT>(Ms + ((k + 1) & 1) * BS, gLe + (size_t)(k + 1) * W * W, tid);
+            stage_padded<W, NT>(Ms + ((k + 1) & 1) * BS, gLe + (size_t)(k + 1) * W * W, tid);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
@@ -638,10 +697,12 @@ static hipError_t launch_adjoint_w(const mcnegf_kernel& k, const GradBuffers& gb
     {
         // one workgroup of lead columns, then the dense ones
         MCNEGF_TIMED("adjoint_solve_kernel", s);
-        if constexpr (W == 16 || W == 32) {
-            // 64 columns per workgroup: W / 8 wavefronts of 32 / W tiles of 16
+        if constexpr (W >= 16) {
+            // 64 columns per workgroup: P / 8 wavefronts of 32 / P tiles of 16.  Ahead of the
+            // VALU at every width it pads, by the least at 17 (2.69 -> 1.74 ms, see above, with
+            // the VALU's registers held to two wavefronts).
             hipLaunchKernelGGL(adjoint_mfma_kernel<W>, dim3(1 + (k.N + 63) / 64, k.nE),
-                               dim3(8 * W), 0, s, a);
+                               dim3(8 * padded(W)), 0, s, a);
         } else {
             hipLaunchKernelGGL(adjoint_solve_kernel<W>, dim3(1 + (k.N + 31) / 32, k.nE), dim3(64),
                                0, s, a);
