@@ -77,11 +77,21 @@ struct StagedBlock {
     }
 };
 
+// Whether the LDS of whole slices and two staged blocks would hold fewer wavefronts than the
+// registers do, and cost time by it.  Then a slice goes through the ring a few rows at a time and
+// one block is staged, the next waiting in registers (a wavefront's LDS accesses are in order, so
+// it may overwrite a block that it has read).  |G|^2, N = 2400, 64 energies: W = 26 2.50 -> 2.01
+// ms, W = 31 4.69 -> 2.73 ms, but W = 17 1.16 -> 1.27 and W = 20 1.53 -> 1.61 ms, where four to six
+// wavefronts per CU fit the LDS.  Complex G, 16 energies: W = 20 1.67 -> 1.08 ms (two sweeps 1.35),
+// W = 17 .. 19 1 to 2 % slower, W = 21 .. 31 equal within 2 %.
+template <int W, bool STORE_G>
+constexpr bool kSmallLds = W >= (STORE_G ? 20 : 26);
+
 // Exit weights into L of one energy, on one wavefront: the columns of slice 0, X = G_{k,0} (W x W
 // in LDS, lanes over its entries), go down the wire by themselves, and row y of slice k weighs
 // sum_a Re conj(X_ya) (Gamma X^T)_ay.  As a chain of its own it stays off the wavefront that
 // stores those columns (the longest one).
-template <int W>
+template <int W, bool ONE>
 __device__ inline void exit_left_chain(lds_double* Ms, lds_double* X,
                                        const double2* __restrict__ gRe,
                                        const double2* __restrict__ Gde,
@@ -107,7 +117,7 @@ __device__ inline void exit_left_chain(lds_double* Ms, lds_double* X,
     StagedBlock<W, 64> st;
     st.load(gRe + (size_t)min(1, L - 1) * W * W, lane);
     for (int k = 0; k < L; ++k) {
-        lds_double* M = Ms + (k & 1) * BS;
+        lds_double* M = Ms + (ONE ? 0 : (k & 1) * BS);
         st.write(M, lane);  // block k + 1
         st.load(gRe + (size_t)min(k + 2, L - 1) * W * W, lane);
         __syncthreads();  // one wavefront: orders the LDS accesses
@@ -181,19 +191,26 @@ __global__ void __launch_bounds__(64) fullinv_kernel(const double2* __restrict__
     const double* gme = gam_lead + (size_t)e * W * W;
     const double mt = -t;
     constexpr int BS = 2 * W * W;  // doubles per staged block
-    __shared__ double Ms_raw[2 * BS];
+    constexpr bool SMALL = kSmallLds<W, STORE_G>;
+    constexpr int NB = SMALL ? 1 : 2;
+    __shared__ double Ms_raw[NB * BS];
     lds_double* Ms = (lds_double*)Ms_raw;
     // what is stored per entry, and a ring of rows whose transposed entries wait until FR
-    // aligned rows (whole 128-byte lines of the transposed row) are there
+    // aligned rows (whole 128-byte lines of the transposed row) are there, PR rows of a slice
+    // at a time
     typedef typename std::conditional<STORE_G, double2, double>::type Entry;
     constexpr int FR = 128 / sizeof(Entry);
-    constexpr int RB = FR + W - 1;
-    __shared__ Entry Tr[RB][65];
+    constexpr int PR = !SMALL ? W : STORE_G ? 4 : 8;
+    constexpr int RB = FR + PR - 1;
+    constexpr int CH = STORE_G ? 0 : (W <= 16 ? 4 : 3) * W * W;  // the chain's blocks (doubles)
+    constexpr int RS = RB * 65 < CH ? (CH + 64) / 65 : RB;
+    __shared__ Entry Tr[RS][65];
+    static_assert(!SMALL || sizeof(Ms_raw) + sizeof(Tr) <= 160 * 1024 / (STORE_G && W <= 23 ? 8 : 4),
+                  "the LDS holds as many wavefronts as the registers: eight, or four, per CU");
     if constexpr (!STORE_G) {
-        static_assert((W <= 16 ? 4 : 3) * W * W <= RB * 65, "the chain's blocks fit the ring");
         if (tile < 0) {
             lds_double* X = (lds_double*)&Tr[0][0];
-            exit_left_chain<W>(Ms, X, gRe, Gde, gme, L, mt, wL + (size_t)e * N);
+            exit_left_chain<W, SMALL>(Ms, X, gRe, Gde, gme, L, mt, wL + (size_t)e * N);
             return;  // the whole workgroup
         }
     }
@@ -207,43 +224,52 @@ __global__ void __launch_bounds__(64) fullinv_kernel(const double2* __restrict__
     double2 v[W];
 #pragma unroll
     for (int y = 0; y < W; ++y) v[y] = Gde[((size_t)l * W + y) * W + y0];
-    StagedBlock<W, 64> st;  // block k + 1 at the top of slice k (the last one again past the end)
+    // block k + 1 (with one buffer block k) at the top of slice k; the last one again past the end
+    StagedBlock<W, 64> st;
     st.load(gRe + (size_t)kmin * W * W, lane);
-    st.write(Ms, lane);
-    st.load(gRe + (size_t)min(kmin + 1, L - 1) * W * W, lane);
+    if constexpr (NB == 2) {
+        st.write(Ms, lane);
+        st.load(gRe + (size_t)min(kmin + 1, L - 1) * W * W, lane);
+    }
     for (int k = kmin; k < L; ++k) {
-        __syncthreads();  // block k staged; the other buffer is free
-        const int b = (k - kmin) & 1;
-        st.write(Ms + (b ^ 1) * BS, lane);
-        st.load(gRe + (size_t)min(k + 2, L - 1) * W * W, lane);
+        __syncthreads();  // the buffer that is written next is free
+        const int b = NB == 2 ? (k - kmin) & 1 : 0;
+        st.write(Ms + (NB == 2 ? (b ^ 1) * BS : 0), lane);
+        st.load(gRe + (size_t)min(k + NB, L - 1) * W * W, lane);
+        if constexpr (NB == 1) __syncthreads();
         block_matvec<W>(v, Ms + b * BS, mt, k > l);
-        const int base = (k * W) % RB;
 #pragma unroll
-        for (int y = 0; y < W; ++y) {
-            Entry o;
-            if constexpr (STORE_G) o = v[y];
-            else o = cabs2(v[y]);
-            if (valid && k >= l) Oe[(size_t)(k * W + y) * ldO + col] = o;
-            Tr[base + y < RB ? base + y : base + y - RB][lane] = o;
-        }
-        __syncthreads();  // one wavefront: orders the LDS accesses
-        const int end = (k + 1) * W;
-        while (pending + FR <= end || (k == L - 1 && pending < end)) {
-            const int r = pending + tr;
-            const int at = pending % RB + tr;
-            const Entry* row = Tr[at < RB ? at : at - RB];
-            Entry* dst = Oe + (size_t)(wave_first + tc) * ldO + r;
-            if (pending >= below && pending + FR <= end) {  // every entry is stored
-#pragma unroll 8
-                for (int c = 0; c < 64; c += 64 / FR) dst[(size_t)c * ldO] = row[c + tc];
-            } else {
-#pragma unroll 1
-                for (int c = 0; c < 64; c += 64 / FR) {
-                    const int j = wave_first + c + tc;
-                    if (j < N && r < end && r >= (j / W + 1) * W) dst[(size_t)c * ldO] = row[c + tc];
-                }
+        for (int p = 0; p < W; p += PR) {
+            const int base = (k * W + p) % RB;
+#pragma unroll
+            for (int y = p; y < (p + PR < W ? p + PR : W); ++y) {
+                Entry o;
+                if constexpr (STORE_G) o = v[y];
+                else o = cabs2(v[y]);
+                if (valid && k >= l) Oe[(size_t)(k * W + y) * ldO + col] = o;
+                Tr[base + y - p < RB ? base + y - p : base + y - p - RB][lane] = o;
             }
-            pending += FR;
+            __syncthreads();  // one wavefront: orders the LDS accesses
+            const int end = k * W + (p + PR < W ? p + PR : W);
+            while (pending + FR <= end || (end == N && pending < end)) {
+                const int r = pending + tr;
+                const int at = pending % RB + tr;
+                const Entry* row = Tr[at < RB ? at : at - RB];
+                Entry* dst = Oe + (size_t)(wave_first + tc) * ldO + r;
+                if (pending >= below && pending + FR <= end) {  // every entry is stored
+#pragma unroll 8
+                    for (int c = 0; c < 64; c += 64 / FR) dst[(size_t)c * ldO] = row[c + tc];
+                } else {
+#pragma unroll 1
+                    for (int c = 0; c < 64; c += 64 / FR) {
+                        const int j = wave_first + c + tc;
+                        if (j < N && r < end && r >= (j / W + 1) * W)
+                            dst[(size_t)c * ldO] = row[c + tc];
+                    }
+                }
+                pending += FR;
+            }
+            if (p + PR < W) __syncthreads();
         }
     }
     if (STORE_G) return;
@@ -385,7 +411,8 @@ __global__ void __launch_bounds__(64 * NW, 2) fullinv_mfma_kernel(const double2*
     const int cg0 = blockIdx.y * NW * 16 * TC;  // the workgroup's first column
     const int c0 = cg0 + (tid >> 6) * 16 * TC;  // this wavefront's first column
     const int kmin = cg0 / W;
-    const bool slice0 = !STORE_G && !BOTH && cg0 == 0;  // its first wavefront holds the columns of slice 0
+    // the workgroup whose first wavefront holds the columns of slice 0
+    const bool slice0 = !STORE_G && !BOTH && cg0 == 0;
     const size_t eb = (size_t)e * L * W * W;
     const double2* gLe = gL + eb;
     const double2* gRe = gR + eb;
