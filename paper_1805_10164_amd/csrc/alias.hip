@@ -282,11 +282,15 @@ __device__ inline double kernel_weight(const AliasArgs& a, int e, int row, int i
 // kernel); the order of the items, and with it the table, depends on BT alone.
 // Wavefronts per SIMD the registers are held to: all eight with 128 threads per row (1.04 ->
 // 1.02 ms at W = 10, N = 1000, 256 energies); 512 threads spill sooner (6.1 -> 6.4 ms over six
-// W = 8 wires when held to 6 or 8).
-constexpr int alias_waves(int BT) { return BT == 128 ? 8 : 1; }
+// W = 8 wires when held to 6 or 8), and so does the longest biased row of 128 threads: at seven
+// wavefronts N = 1000, 256 energies 1.11 -> 1.06 ms, and 1024 outcomes, whose LDS leaves seven in any
+// case, 1.18 -> 1.04 ms (1.08 with all items checked).
+constexpr int alias_waves(int BT, int KM, bool bias) {
+    return BT != 128 ? 1 : bias && KM == 8 ? 7 : 8;
+}
 
 template <int BT, int KM, int KP, bool kBias = false>
-__global__ void __launch_bounds__(BT, alias_waves(BT)) alias_build_kernel(AliasArgs a) {
+__global__ void __launch_bounds__(BT, alias_waves(BT, KM, kBias)) alias_build_kernel(AliasArgs a) {
     constexpr bool kLong = KM > 8;  // rows above BT * 8 outcomes
     extern __shared__ double smem[];
     __shared__ double sd[BT / 64];  // one partial per wavefront
