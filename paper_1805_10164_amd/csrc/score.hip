@@ -145,17 +145,20 @@ __device__ inline void wave_sums(double (&out)[(W + 7) / 8], const double2 (&v)[
 // on the chain: the slice's G entries, counts and y rows are loaded AHEAD slices early and its gL
 // block one slice early; the sums of a slice's rows share their exchanges.  W = 5, N = 615, 48
 // energies: 1.33 -> 0.41 ms, 2.9 TB/s of the 1.2 GB it moves.
-// Loads ahead cost registers: up to W = 12 two wavefronts per SIMD hold them, at W = 13 .. 16 they
-// would leave one (W = 16, N = 640, 128 energies: 1.79 ms with, 1.27 ms without, 1.54 ms before),
-// at W = 17 .. 24 one is left either way (W = 20, N = 800, 64 energies: 2.2 -> 1.43 ms) and above
-// that they no longer fit (W = 32, N = 960, 64 energies: 4.16 -> 3.37 ms without).
+// Loads ahead cost registers: up to W = 12 two wavefronts per SIMD hold them (W = 8 and 12 spill a
+// few); above that they would leave one (W = 16, N = 640, 128 energies: 1.79 ms with, 1.27 ms
+// without).  There a slice's rows are taken with their loads, one at a time up to W = 16 and four at
+// a time above, where fewer chains are in flight: N = 640, 64 energies, W = 17 0.91 -> 0.79 ms, W = 24
+// 1.38 -> 1.21 ms (both with loads ahead before), W = 32 2.13 -> 1.96 ms (one row at a time before);
+// W = 26, 8 energies 1.55 -> 1.40 ms.
 template <int W>
 __global__ void __launch_bounds__(64, W <= 16 ? 2 : 1) score_solve_kernel(
     const double2* __restrict__ gL, const double2* __restrict__ Gc,
     const uint32_t* __restrict__ counts, const double* __restrict__ sv,
     const double* __restrict__ wL, const double* __restrict__ wR, int L, double t, int64_t ld,
     int64_t ldY, uint32_t inject_lead, double2* __restrict__ Y) {
-    constexpr bool EARLY = W <= 12 || (W > 16 && W <= 24);
+    constexpr bool EARLY = W <= 12;
+    constexpr int ROWS = W <= 16 ? 1 : 4;  // rows whose loads go together without EARLY
     constexpr int AHEAD = W <= 4 ? 4 : (W <= 8 ? 2 : 1);
     constexpr int NM = (W * W + 63) / 64;
     const int N = W * L;
@@ -249,7 +252,7 @@ __global__ void __launch_bounds__(64, W <= 16 ? 2 : 1) score_solve_kernel(
                 double2 v = cmk(q * gj.x, -q * gj.y);
                 if (dense && j == c) v.y -= 2.0 * mu;
                 z[r] = cmk(v.x - t * y[r].x, v.y - t * y[r].y);
-                if (!EARLY) __builtin_amdgcn_sched_barrier(0);  // one row's registers at a time
+                if (!EARLY && r % ROWS == ROWS - 1) __builtin_amdgcn_sched_barrier(0);
             }
             if (EARLY && k + AHEAD < L) load_entries(u, k + AHEAD);
             __builtin_amdgcn_sched_barrier(0);
@@ -292,7 +295,7 @@ __global__ void __launch_bounds__(64, W <= 16 ? 2 : 1) score_solve_kernel(
                 for (int r = 0; r < W; ++r) {
                     if (!EARLY) yk[u][r] = Ye[(size_t)(k * W + r) * ldY + cl];
                     y[r] = cmk(fma(-t, z[r].x, yk[u][r].x), fma(-t, z[r].y, yk[u][r].y));
-                    if (!EARLY) __builtin_amdgcn_sched_barrier(0);
+                    if (!EARLY && r % ROWS == ROWS - 1) __builtin_amdgcn_sched_barrier(0);
                 }
             }
 #pragma unroll
@@ -307,9 +310,10 @@ __global__ void __launch_bounds__(64, W <= 16 ? 2 : 1) score_solve_kernel(
                 double sum[(W + 7) / 8];
 #pragma unroll
                 for (int r = 0; r < W; ++r) {
-                    const double2 v = cmul(EARLY ? gk[EARLY ? r : 0] : Ge[(size_t)(k * W + r) * ld], y[r]);
+                    const double2 v =
+                        cmul(EARLY ? gk[EARLY ? r : 0] : Ge[(size_t)(k * W + r) * ld], y[r]);
                     z[r] = cmk(dense ? v.x : 0.0, dense ? v.y : 0.0);
-                    if (!EARLY) __builtin_amdgcn_sched_barrier(0);
+                    if (!EARLY && r % ROWS == ROWS - 1) __builtin_amdgcn_sched_barrier(0);
                 }
                 wave_sums<W>(sum, z, tid);
                 const int row = 4 * ((tid >> 2) & 1) + 2 * ((tid >> 3) & 1) + ((tid >> 4) & 1);
