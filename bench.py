@@ -169,7 +169,7 @@ def kernel_work(name, wl, walk_steps):
         # factorization N^3/3 plus the two forward substitutions of the bordered rows, 2 N^2
         return "mfma", nE * (N ** 3 / 3.0 + 2.0 * N * N) / 1e12, "TFLOP"
     if name == "fullinv_kernel":
-        # all blocks of G: L*(L-1) complex W x W block products per energy (the kernel needs half)
+        # all blocks of G: L*(L-1) complex W x W block products per energy
         return "alu", nE * 8.0 * W ** 3 * wl.L * (wl.L - 1) / 1e12, "TFLOP"
     if name == "alias_build_kernel":
         # read gamma_i |G_ji|^2 rows and write one 4-byte entry plus 2 low threshold bytes per outcome
@@ -177,13 +177,17 @@ def kernel_work(name, wl, walk_steps):
     return None
 
 
+# The share of kernel_work that an FP64 build has to do: G = G^T, so the full inverse needs the
+# blocks on and below the diagonal only.
+NEEDED_SHARE = {"fullinv_kernel": 0.5}
+
+
 def roofline(name, wl, ms_per_launch, walk_steps):
     w = kernel_work(name, wl, walk_steps)
     if w is None:
         return None
     bound, amount, unit = w
-    if name == "fullinv_kernel":
-        amount *= 0.5  # G = G^T: the blocks on and below the diagonal only
+    amount *= NEEDED_SHARE.get(name, 1.0)
     if unit == "GB":
         achieved = amount / (ms_per_launch * 1e-3)
         r = {"kernel": name, "bound": bound, "achieved": achieved, "peak": HBM_PEAK_GBS,
@@ -811,7 +815,8 @@ def scale_bench(torch, dev, warmup, with_cpu, seed, timed_batches=None, fp32=Tru
     chol_ms = per_kernel["cholesky_kernel"]["ms_per_batch"]
     chol_flop = nE * (wl.N ** 3 / 3.0 + 2.0 * wl.N * wl.N)
     fi_ms = per_kernel["fullinv_kernel"]["ms_per_launch"]
-    fi_flop = nE * 4.0 * wl.W ** 3 * wl.L * (wl.L - 1)  # G = G^T: half of G's blocks
+    fi_flop = kernel_work("fullinv_kernel", wl.replace(n_energies=nE), 0)[1] * 1e12 * \
+        NEEDED_SHARE["fullinv_kernel"]
     I_mc, s_mc = float(o[:, 0, 0].sum()), float(np.sqrt(np.sum(o[:, 0, 1] ** 2)))
     I_d = float(o[:, 1, 0].sum())
 

@@ -261,7 +261,7 @@ int32_t mc_negf_current(const mcnegf_kernel* k, int32_t mode, uint32_t inject_le
 
 /*
  * Bytes of device workspace mc_negf_grad needs for the built kernel `k` (host only): the
- * complex G [chunk][N][p_pitch], the adjoint solves [chunk][N][roundup(N + W, 16)] and
+ * complex G [chunk][N][p_pitch], the adjoint solves [chunk][N][roundup(N + 2 W, 16)] and
  * O(chunk N) vectors for `chunk` energies at a time, plus O(nE N) per-energy derivatives.
  * mc_negf_grad_workspace_bytes gives the size for all energies at once (chunk = nE),
  * mc_negf_grad_workspace_bytes_chunk for 1 <= chunk <= nE.  MCNEGF_EINVAL for a bad handle.

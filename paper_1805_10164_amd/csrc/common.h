@@ -123,7 +123,9 @@ constexpr int kRefineChunk = 8;  // energies refined at a time
 // gradient workspace (caller-owned, separate from the build workspace)
 struct GradBuffers {
     double2* G;       // [chunk][N][ld] complex G, row-major
-    double2* Y;       // [chunk][N][ldY] adjoint solves, column c: Q (c < N) or R (c = N + b)
+    // [chunk][N][ldY]; mc_negf_grad keeps the columns sq .. sq + W - 1 (Q's lead columns) and
+    // N .. N + W - 1 (R's) of it, mc_negf_grad_mc all N + 2 W of its solves
+    double2* Y;
     double2* part_k;  // [chunk][2][N] dense and diagonal parts of K per site
     double* part_p;   // [chunk][2][N] (P v)_i, (P u)_i
     double* xl;       // [chunk][2][ld] x, lambda

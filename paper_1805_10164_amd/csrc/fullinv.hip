@@ -21,12 +21,13 @@
 // cores the first workgroup of an energy forms them from its columns as it passes).
 // Half the block products and one sweep instead of two: 0.75 -> 0.54 ms at W = 10, N = 1000,
 // 256 energies (3.8 TB/s of |G|^2 written), 2.82 -> 2.32 ms over six W = 8 wires.  With few
-// wavefronts the chain of slices bounds it (W = 7, 61 slices, 37 energies: 0.10 ms before and
-// after).
+// wavefronts the chain of slices bounds it, and a slice of the chain has become longer (the ring,
+// two waits): W = 7, 61 slices, 37 energies 0.102 -> 0.106 ms, W = 1, N = 2400, 4 energies 0.51 ->
+// 0.60 ms.
 // The block products run on the FP64 VALU: the operands live in registers and LDS, and
 // gfx950's FP64 matrix-core rate equals its FP64 FMA rate, so padding W up to a 16x16x4 MFMA
-// shape would only add work.  Up to W = 24 the column and the product fit the register file;
-// at W = 32 a few values spill.
+// shape would only add work.  Up to W = 27 the column and the product fit the register file (from
+// W = 19 on a SIMD holds one wavefront); from W = 28 on values spill, 0.5 KB per lane at W = 31.
 #include <type_traits>
 
 #include "common.h"
