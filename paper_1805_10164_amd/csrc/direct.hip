@@ -824,13 +824,14 @@ __global__ void __launch_bounds__(64 * CH_SOLVE_WAVES, 2) cholesky_solve_kernel(
 
 // Update: one workgroup per tile of 32 F x 32 F entries, four wavefronts of F x F
 // accumulators (16 F x 16 F entries) each.  A 16x16x4 product occupies a SIMD for 64 clocks,
-// so a 128 x 128 tile, 32 products per SIMD and 8 columns, needs 16 KB of operands per 2048 clocks:
-// bandwidth is not short, latency is.  The 8-column steps are staged in LDS (double-buffered, one barrier per
-// step) from registers loaded four steps ahead; two workgroups share a CU (four of 64 x 64, which
-// need twice the operands but are less often all at their reads and writes of V at once; the
-// launch takes the one that is faster).  In a step lane group g takes the positions 2 g, 2 g + 1
-// of both operands (the same permutation of the contracted columns on both sides); a staged row
-// is 64 bytes, its 16-byte pieces swizzled by the row so that eight rows spread over all banks.
+// so a 128 x 128 tile, 32 products per SIMD and 8 columns, needs 16 KB of operands per 2048
+// clocks: bandwidth is not short, latency is.  The 8-column steps are staged in LDS
+// (double-buffered, one barrier per step) from registers loaded four steps ahead; two workgroups
+// share a CU (four of 64 x 64, which need twice the operands but are less often all at their reads
+// and writes of V at once; the launch takes the one that is faster).  In a step lane group g takes
+// the positions 2 g, 2 g + 1 of both operands (the same permutation of the contracted columns on
+// both sides); a staged row is 64 bytes, its 16-byte pieces swizzled by the row so that eight rows
+// spread over all banks.
 template <int F>
 __global__ void __launch_bounds__(256, F == 4 ? 2 : 4) cholesky_update_kernel(CholArgs a) {
     constexpr int TS = 32 * F;  // tile side
